@@ -1,0 +1,469 @@
+"""Performance cases of the GCPSL library: what its users run, through the public binding.
+
+Four kinds of pass:
+
+  round    one local round of every cluster: Context.sample + Context.step (sampling, gather, client and server
+           forward, loss, server and client backward, SGD update), all clusters side by side;
+  serial   the same round with the clusters run one after another (Context.step_replica), the sequential execution
+           that the concurrent one is compared with and the tail of an epoch in which one cluster is left;
+  window   Context.sample over a window of steps (sampling and gather only), as a caller that stages ahead does;
+  fuse     gcpsl.fuse_replicas: the sample-weighted average of C replicas, written back to all of them.
+
+Models: the split CNNs with the narrow and the wide residual server, ResNet-18 split after its second stage, and small
+ragged networks (image sizes and channel counts that fill no tile).  Every pass of a round works on freshly sampled
+examples of the cluster's pool and on the parameters the pass before left behind.
+
+Inputs are synthetic and seeded: class-mean images plus noise, balanced random labels, uniform +-1/sqrt(fan-in)
+parameters (the PyTorch default bound), normalisation layers at gamma 1, beta 0.
+"""
+from __future__ import annotations
+
+import math
+
+import numpy as np
+import torch
+
+from paper_2609_29395_amd import gcpsl
+
+# ------------------------------------------------------------------ models
+
+_CLIENT = [("conv", 3, 32, False), ("conv", 32, 64, False), ("maxpool",)]
+
+
+def _model(case):
+    """(layers, cut, image side, classes) of a case's network."""
+    m = case["model"]
+    if m == "narrow":
+        return (_CLIENT + [("conv", 64, 128, False), ("conv", 128, 128, False), ("maxpool",), ("avgpool",),
+                           ("linear", 128, 10)], 3, 32, 10)
+    if m == "wide":
+        return (_CLIENT + [("conv", 64, 256, False)] + [("conv", 256, 256, True)] * 3 +
+                [("maxpool",), ("avgpool",), ("linear", 256, 10)], 3, 32, 10)
+    if m == "resnet18":
+        layers, cin = [("conv", 3, 64, False), ("gnorm", 64, 32)], 64
+        for st, w in enumerate((64, 128, 256, 512)):
+            for b in range(2):
+                layers.append(("block", cin, w, 2 if st and not b else 1, 32 if st < 2 else 0))
+                cin = w
+        return layers + [("avgpool",), ("linear", 512, 10)], 6, 32, 10
+    # a small network of two client convs and a residual server pair: side, widths and classes of the case
+    a, b, c, n = case["w1"], case["w2"], case["w3"], case["classes"]
+    if m == "ragged":
+        return ([("conv", 3, a, False), ("conv", a, b, False), ("maxpool",), ("conv", b, c, False),
+                 ("conv", c, c, True), ("maxpool",), ("avgpool",), ("linear", c, n)], 3, case["side"], n)
+    if m == "ragged_norm":  # group norm in the client segment, batch norm in the server segment
+        return ([("conv", 3, a, False), ("gnorm", a, 4), ("conv", a, b, False), ("gnorm", b, b // 8),
+                 ("conv", b, c, False), ("bnorm", c), ("conv", c, c, False), ("bnorm", c), ("avgpool",),
+                 ("linear", c, n)], 4, case["side"], n)
+    if m == "stage":  # residual blocks: a strided one with group norm, one with batch norm
+        return ([("conv", 3, a, False), ("gnorm", a, a // 8), ("block", a, b, 2, b // 8), ("block", b, c, 1, 0),
+                 ("avgpool",), ("linear", c, n)], 3, case["side"], n)
+    raise ValueError(m)
+
+
+def _params(layers):
+    """[(layer, tag, shape, fan-in or None for gamma 1 / beta 0)] in the order of the parameter vector."""
+    out = []
+
+    def norm(i, tag, ch):
+        out.extend([(i, tag + "w", (ch,), None), (i, tag + "b", (ch,), None)])
+
+    def conv(i, tag, co, taps, ci):
+        out.extend([(i, "w" + tag, (co, taps, taps, ci), taps * taps * ci), (i, "b" + tag, (co,), taps * taps * ci)])
+
+    for i, s in enumerate(layers):
+        if s[0] == "conv":
+            conv(i, "", s[2], 3, s[1])
+        elif s[0] in ("gnorm", "bnorm"):
+            norm(i, "n", s[1])
+        elif s[0] == "block":
+            conv(i, "1", s[2], 3, s[1])
+            norm(i, "n1", s[2])
+            conv(i, "2", s[2], 3, s[2])
+            norm(i, "n2", s[2])
+            if s[3] != 1 or s[1] != s[2]:
+                conv(i, "p", s[2], 1, s[1])
+                norm(i, "np", s[2])
+        elif s[0] == "linear":
+            out.extend([(i, "w", (s[2], s[1]), s[1]), (i, "b", (s[2],), s[1])])
+    return out
+
+
+def _n_params(layers):
+    return sum(math.prod(p[2]) for p in _params(layers))
+
+
+def _state_channels(layers):
+    """Channels of every batch norm, in the order of the normalisation state."""
+    out = []
+    for s in layers:
+        if s[0] == "bnorm":
+            out.append(s[1])
+        elif s[0] == "block" and s[4] == 0:
+            out += [s[2]] * (3 if s[3] != 1 or s[1] != s[2] else 2)
+    return out
+
+
+def _conv_sizes(layers, side):
+    """[(output pixels, output channels, taps x input channels, is first layer)] of every conv."""
+    out, h = [], side
+    for i, s in enumerate(layers):
+        if s[0] == "conv":
+            out.append((h * h, s[2], 9 * s[1], i == 0))
+        elif s[0] == "block":
+            h //= s[3]
+            out += [(h * h, s[2], 9 * s[1], False), (h * h, s[2], 9 * s[2], False)]
+            if s[3] != 1 or s[1] != s[2]:
+                out.append((h * h, s[2], s[1], False))
+        elif s[0] == "maxpool":
+            h //= 2
+    return out
+
+
+# ------------------------------------------------------------------- cases
+
+def listed():
+    return [
+        # the smallest call: the tests' two 8-example clusters of 8 x 8 images, where launches and latency count
+        dict(name="tiny_f32", kind="round", model="ragged", dtype="f32", C=2, B=8, side=8, w1=8, w2=16, w3=16,
+             classes=4),
+        # odd sizes that fill no tile, single precision (the ragged parity shapes)
+        dict(name="ragged_f32", kind="round", model="ragged", dtype="f32", C=3, B=20, side=12, w1=8, w2=24, w3=136,
+             classes=7),
+        # the same shapes in bf16 with group and batch norm
+        dict(name="ragged_norm_bf16", kind="round", model="ragged_norm", dtype="bf16", C=3, B=20, side=12, w1=8,
+             w2=24, w3=136, classes=7),
+        # the single-workload GPSL baseline: one cluster
+        dict(name="gpsl_f32", kind="round", model="narrow", dtype="f32", C=1, B=64),
+        # four clusters, single precision: the ordinary run
+        dict(name="gcpsl4_f32", kind="round", model="narrow", dtype="f32", C=4, B=64),
+        # eight clusters, bf16
+        dict(name="gcpsl8_bf16", kind="round", model="narrow", dtype="bf16", C=8, B=64),
+        # the benchmark's workload: sixteen clusters, wide residual server, bf16
+        dict(name="gcpsl16_bf16", kind="round", model="wide", dtype="bf16", C=16, B=128),
+        # clusters one after another: what a cluster costs alone
+        dict(name="serial_bf16", kind="serial", model="wide", dtype="bf16", C=2, B=128),
+        # the paper's model and recipe in both precisions
+        dict(name="resnet18_f32", kind="round", model="resnet18", dtype="f32", C=4, B=64),
+        dict(name="resnet18_bf16", kind="round", model="resnet18", dtype="bf16", C=4, B=64),
+        # the fusion of the benchmark's sixteen replicas
+        dict(name="fuse16", kind="fuse", C=16, P=1939914),
+        # the benchmark's batches staged a fusion interval ahead
+        dict(name="window50_bf16", kind="window", model="wide", dtype="bf16", C=16, B=128, steps=50, pool=16384),
+    ]
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _cost(case):
+    """A bound on a case's time in seconds at modest rates, to keep drawn cases within the listed ones."""
+    w = work(case)
+    rate = {"f32": 60e12, "bf16": 350e12 if case.get("model") == "resnet18" else 900e12}[case.get("dtype", "f32")]
+    return w["flops"] / rate + w["bytes"] / 3e12
+
+
+def draw(rng):
+    while True:
+        u = rng.random()
+        if u < 0.4:  # the CNNs: one to sixteen clusters, any batch
+            case = dict(kind="serial" if rng.random() < 0.15 else "round", model=rng.choice(["narrow", "wide"]),
+                        dtype=rng.choice(["f32", "bf16"]), C=_log(rng, 1, 16), B=_log(rng, 12, 128))
+        elif u < 0.6:
+            case = dict(kind="round", model="resnet18", dtype=rng.choice(["f32", "bf16"]), C=rng.randint(1, 4),
+                        B=_log(rng, 12, 64))
+        elif u < 0.85:
+            case = dict(kind="round", model=rng.choice(["ragged", "ragged_norm", "stage"]), dtype=rng.choice(["f32", "bf16"]),
+                        C=rng.randint(1, 6), B=_log(rng, 5, 100), side=4 * rng.randint(2, 5), w1=8 * rng.randint(1, 4),
+                        w2=8 * rng.randint(1, 8), w3=8 * rng.randint(2, 24), classes=rng.randint(2, 16))
+        elif u < 0.95:
+            case = dict(kind="fuse", C=_log(rng, 2, 64), P=_log(rng, 1000, 16000000))
+            if case["C"] * case["P"] > 16 * 16000000:
+                continue
+        else:
+            case = dict(kind="window", model="wide", dtype="bf16", C=_log(rng, 2, 16), B=_log(rng, 12, 128),
+                        steps=_log(rng, 2, 50), pool=4096)
+        if _cost(case) < 0.012:
+            return case
+
+
+def _gradient_told(case):
+    """Whether the momentum (the first round's gradient) is an output.  Not for residual blocks in bf16: one fp32 ulp
+    on the parameters moves ResNet-18's gradient by 0.19 of its norm there (and it is 0.24 off the 64-bit one), so no
+    two orders of summation could be compared by it; the losses, updated parameters and batch-norm statistics are."""
+    return not (case["model"] in ("resnet18", "stage") and case["dtype"] == "bf16")
+
+
+# ------------------------------------------------------------------ inputs
+
+def _recipe(case):
+    """Optimiser and loss settings: the paper's recipe for the normalised networks, at the learning rate a warm-up
+    starts from (gradients of such deep networks are sensitive to every rounding, and a large first update would pass
+    that on to the second round); plain SGD with momentum otherwise."""
+    if case["model"] in ("resnet18", "ragged_norm", "stage"):
+        return dict(lr=1e-4, momentum=0.9, nesterov=True, weight_decay=5e-4, label_smoothing=0.1)
+    return dict(lr=0.05, momentum=0.9, nesterov=False, weight_decay=0.0, label_smoothing=0.0)
+
+
+def _inputs(case, seed):
+    """Host inputs of a round: images, labels, client of each example, cluster of each client, theta_0."""
+    layers, _, side, classes = _model(case)
+    C, B = case["C"], case["B"]
+    rng = np.random.default_rng([int(seed), 11])
+    K = 16 * C
+    n = max(case.get("pool", 0), 4 * C * B, 32 * C)
+    n += -n % classes
+    labels = rng.permutation(np.repeat(np.arange(classes, dtype=np.int32), n // classes))
+    images = rng.standard_normal((n, side, side, 3), dtype=np.float32)
+    images *= np.float32(0.5)
+    images += rng.standard_normal((classes, side, side, 3), dtype=np.float32)[labels]
+    clusters = (np.arange(K) % C).astype(np.int32)
+    # every cluster holds the same number of examples, spread at random over its 16 clients
+    clients = (rng.permutation(n) % C + C * rng.integers(0, 16, n)).astype(np.int32)
+    theta = []
+    for _, tag, shape, fan in _params(layers):
+        k = math.prod(shape)
+        if fan is None:
+            theta.append(np.full(k, 1.0 if tag.endswith("w") else 0.0, dtype=np.float32))
+        else:
+            theta.append(rng.uniform(-1 / math.sqrt(fan), 1 / math.sqrt(fan), k).astype(np.float32))
+    return images, labels, clients, clusters, np.concatenate(theta)
+
+
+def _norm_state0(layers):
+    out = [np.concatenate([np.zeros(c), np.ones(c), np.zeros(1)]) for c in _state_channels(layers)]
+    return np.concatenate(out).astype(np.float32) if out else None
+
+
+def _fuse_inputs(case, seed):
+    g = torch.Generator().manual_seed(int(seed))
+    base = torch.randn(case["P"], generator=g) * 0.05
+    theta = torch.stack([base + 0.01 * torch.roll(base, 17 * (n + 1)) for n in range(case["C"])])
+    weights = np.random.default_rng([int(seed), 12]).integers(100, 12000, case["C"])
+    return theta, weights
+
+
+def prepare(case, seed):
+    if case["kind"] == "fuse":
+        theta, weights = _fuse_inputs(case, seed)
+        return dict(kind="fuse", theta=theta.cuda(), weights=weights)
+    layers, cut, side, classes = _model(case)
+    images, labels, clients, clusters, theta = _inputs(case, seed)
+    window = case.get("steps", 1)
+    cfg = dict(K=len(clusters), C=case["C"], B=case["B"], L=classes, H=side, W=side, Cin=3, N_ex=len(labels),
+               layers=layers, cut=cut, dtype=case["dtype"], seed=int(seed) & 0xFFFFFFFF, **_recipe(case))
+    ctx = gcpsl.Context(cfg, images, labels, clients, clusters, theta, max_steps=4096, max_window=window,
+                        norm_state0=_norm_state0(layers))
+    if case["kind"] == "window":
+        return dict(kind="window", ctx=ctx, at=0, steps=window,
+                    idx=torch.empty(window, case["C"], case["B"], dtype=torch.int32, device="cuda"))
+    return dict(kind=case["kind"], ctx=ctx, at=0, C=case["C"], momentum=_gradient_told(case),
+                loss=torch.zeros(case["C"], device="cuda"))
+
+
+def run(state):
+    if state["kind"] == "fuse":
+        gcpsl.fuse_replicas(state["theta"], state["weights"])
+        return state["theta"]
+    ctx, at = state["ctx"], state["at"]
+    if state["kind"] == "window":
+        ctx.sample(at, state["steps"], state["idx"])
+        state["at"] = at + state["steps"]
+        return {"idx": state["idx"], "x": ctx.tensor("x"), "y": ctx.tensor("y")}
+    ctx.sample(at)
+    if state["kind"] == "serial":
+        for n in range(state["C"]):
+            ctx.step_replica(at, n, state["loss"])
+    else:
+        ctx.step(at, state["loss"])
+    state["at"] = at + 1
+    out = {"loss": state["loss"], "theta": ctx.theta}
+    if state["momentum"]:
+        out["momentum"] = ctx.mom
+    if ctx.norm_state is not None:
+        out["norm_state"] = ctx.norm_state
+    return out
+
+
+def work(case):
+    C = case["C"]
+    if case["kind"] == "fuse":
+        return {"bytes": 8.0 * C * case["P"], "flops": 2.0 * C * case["P"]}
+    layers, _, side, _ = _model(case)
+    rows = float(C * case["B"] * case.get("steps", 1))
+    image = 3.0 * side * side
+    if case["kind"] == "window":  # images read once and written once in bf16; ids and labels
+        return {"bytes": rows * (image * (4 + 2) + 12), "flops": 0.0}
+    # forward, weight gradient and (but for the image layer) input gradient of every conv; the head is negligible
+    macs = sum(px * co * k * (2 if first else 3) for px, co, k, first in _conv_sizes(layers, side))
+    state = C * (16.0 * _n_params(layers) + 8.0 * sum(2 * c + 1 for c in _state_channels(layers)))
+    return {"bytes": rows * (image * 4 + 8) + state, "flops": 2.0 * rows * macs}
+
+
+def _decisions(case):
+    """ReLU and max-pool decisions of a round: one per conv output."""
+    layers, _, side, _ = _model(case)
+    return case["C"] * case["B"] * sum(px * co for px, co, _, _ in _conv_sizes(layers, side))
+
+
+def tolerance(case):
+    if case["kind"] == "window":
+        return "exact"  # whole numbers, and images rounded once
+    if case["kind"] == "fuse":
+        return {"rel": 1e-7, "max": 1e-6}  # fp64 sums, one rounding
+    # Measured by moving the inputs one fp32 ulp, which flips bf16 roundings and decisions at ties as another order of
+    # the sums does, over one and two rounds of the listed and 70 drawn cases.
+    if case["dtype"] == "bf16":
+        # losses 5e-4 off for ResNet-18; momentum 0.003 to 0.01 for the CNNs and 0.005 for the small normalised ones
+        return {"rel": 0.03 if _gradient_told(case) else 2e-3}
+    # Sums alone agree to 4e-7.  But a ReLU or max-pool decision at a value within rounding of a tie (about one in 1e7)
+    # moves its gradient entry whole, and one of them outweighs all rounding: the momentum is 2e-7 off without any, up
+    # to 8e-4 with them in the CNNs and 1.1e-2 (a single entry: 0.67) in ResNet-18, which has two dozen a round.
+    if _decisions(case) < 1e5:
+        return {"rel": 1e-5}
+    return {"rel": 0.03, "max": 0.99} if case["model"] == "resnet18" else {"rel": 4e-3}
+
+
+# ------------------------------------------------------------ 64-bit results
+
+_M = (1 << 64) - 1
+
+
+def _mix(z):
+    z &= _M
+    z = ((z ^ (z >> 30)) * 0xBF58476D1CE4E5B9) & _M
+    z = ((z ^ (z >> 27)) * 0x94D049BB133111EB) & _M
+    return z ^ (z >> 31)
+
+
+def _batch(ids, B, seed, n, step):
+    """Example ids of cluster n's batch at a round: positions of a keyed Feistel permutation of its pool (the sampling
+    rule of the library's header)."""
+    size = len(ids)
+    epoch, t = divmod(step, size // B)
+    key = _mix(_mix(_mix(seed + 0x53414D504C45) + n) + epoch)
+    h = (max(1, (size - 1).bit_length()) + 1) // 2
+    mask = (1 << h) - 1
+    out = []
+    for x in range(t * B, t * B + B):
+        while True:
+            left, right = x >> h, x & mask
+            for i in range(4):
+                left, right = right, left ^ (_mix(key ^ ((i + 1) << 32 | right)) & mask)
+            x = left << h | right
+            if x < size:
+                break
+        out.append(ids[x])
+    return np.array(out, dtype=np.int64)
+
+
+def _conv64(x, w, b, stride=1, pad=1):
+    """x [B][C][H][W], w [co][r][s][ci]: the convolution as one matrix product."""
+    co, r = w.shape[:2]
+    n, _, hh, ww = x.shape
+    ho, wo = (hh + 2 * pad - r) // stride + 1, (ww + 2 * pad - r) // stride + 1
+    cols = torch.nn.functional.unfold(x, r, padding=pad, stride=stride)  # [B][ci r s][ho wo]
+    cols = cols.permute(1, 0, 2).reshape(cols.shape[1], -1)
+    y = w.permute(0, 3, 1, 2).reshape(co, -1) @ cols + b[:, None]
+    return y.reshape(co, n, ho, wo).permute(1, 0, 2, 3)
+
+
+def _norm64(z, g, b, groups, stats):
+    if groups:
+        n, c, hh, ww = z.shape
+        zg = z.reshape(n, groups, -1)
+        mean, var = zg.mean(2, keepdim=True), zg.var(2, unbiased=False, keepdim=True)
+        xh = ((zg - mean) / torch.sqrt(var + 1e-5)).reshape(z.shape)
+    else:
+        mean, var = z.mean((0, 2, 3)), z.var((0, 2, 3), unbiased=False)
+        k = z.numel() // z.shape[1]
+        stats.append((mean.detach(), (var * k / (k - 1)).detach()))
+        xh = (z - mean[:, None, None]) / torch.sqrt(var + 1e-5)[:, None, None]
+    return xh * g[:, None, None] + b[:, None, None]
+
+
+def _loss64(layers, p, x, y, eps):
+    """Mean cross-entropy of the network in 64 bits, and every batch norm's (mean, unbiased variance)."""
+    relu, stats = torch.relu, []
+    for i, s in enumerate(layers):
+        q = p.get(i)
+        if s[0] == "conv":
+            z = _conv64(x, q["w"], q["b"])
+            x = z + x if s[3] else z
+            if layers[i + 1][0] not in ("gnorm", "bnorm"):
+                x = relu(x)
+        elif s[0] in ("gnorm", "bnorm"):
+            x = relu(_norm64(x, q["nw"], q["nb"], s[2] if s[0] == "gnorm" else 0, stats))
+        elif s[0] == "block":
+            g, mine = s[4], []
+            u = relu(_norm64(_conv64(x, q["w1"], q["b1"], s[3]), q["n1w"], q["n1b"], g, mine))
+            u = _norm64(_conv64(u, q["w2"], q["b2"]), q["n2w"], q["n2b"], g, mine)
+            if "wp" in q:
+                x = _norm64(_conv64(x, q["wp"], q["bp"], s[3], 0), q["npw"], q["npb"], g, mine)
+            x = relu(u + x)
+            stats += mine
+        elif s[0] == "maxpool":
+            x = torch.nn.functional.max_pool2d(x, 2)
+        elif s[0] == "avgpool":
+            x = x.mean((2, 3))
+        else:
+            x = x @ q["w"].T + q["b"]
+    logp = torch.log_softmax(x, 1)
+    n, k = logp.shape
+    target = torch.full_like(logp, eps / k)
+    target[torch.arange(n, device=x.device), y] += 1 - eps
+    return -(target * logp).sum(1).mean(), stats
+
+
+def exact(case, seed):
+    dev = "cuda" if torch.cuda.is_available() else "cpu"
+    if case["kind"] == "fuse":
+        theta, weights = _fuse_inputs(case, seed)
+        w = torch.as_tensor(weights, dtype=torch.float64, device=dev)
+        mean = torch.zeros(case["P"], dtype=torch.float64, device=dev)
+        for n in range(case["C"]):
+            mean += w[n] * theta[n].to(dev).double()
+        return (mean / w.sum()).expand(case["C"], -1)
+    images, labels, clients, clusters, theta0 = _inputs(case, seed)
+    layers, _, side, _ = _model(case)
+    C, B, owner = case["C"], case["B"], clusters[clients]
+    pools = [np.flatnonzero(owner == n) for n in range(C)]
+    key = int(seed) & 0xFFFFFFFF
+    if case["kind"] == "window":
+        idx = np.stack([np.stack([_batch(pools[n], B, key, n, s) for n in range(C)]) for s in range(case["steps"])])
+        x = torch.from_numpy(images)[torch.from_numpy(idx.reshape(-1))].to(torch.bfloat16).reshape(-1)
+        return {"idx": idx.astype(np.int32), "x": x, "y": labels[idx.reshape(-1)]}
+    r = _recipe(case)
+    loss, theta, mom, state = [], [], [], []
+    for n in range(C):
+        at = _batch(pools[n], B, key, n, 0)
+        x = torch.from_numpy(images[at]).to(dev).double().permute(0, 3, 1, 2)
+        y = torch.from_numpy(labels[at].astype(np.int64)).to(dev)
+        flat = torch.from_numpy(theta0).to(dev).double()
+        p, leaves, off = {}, [], 0
+        for i, tag, shape, _ in _params(layers):
+            k = math.prod(shape)
+            leaf = flat[off:off + k].reshape(shape).clone().requires_grad_(True)
+            p.setdefault(i, {})[tag] = leaf
+            leaves.append(leaf)
+            off += k
+        value, stats = _loss64(layers, p, x, y, r["label_smoothing"])
+        g = torch.cat([t.reshape(-1) for t in torch.autograd.grad(value, leaves)])
+        g = g + r["weight_decay"] * flat
+        loss.append(value.detach())
+        mom.append(g)
+        theta.append(flat - r["lr"] * ((1 + r["momentum"]) * g if r["nesterov"] else g))
+        if stats:
+            state.append(torch.cat([torch.cat([0.1 * m, 0.9 + 0.1 * v, torch.ones(1, dtype=m.dtype, device=dev)])
+                                    for m, v in stats]))
+    out = {"loss": torch.stack(loss), "theta": torch.stack(theta), "momentum": torch.stack(mom)}
+    if state:
+        out["norm_state"] = torch.stack(state)
+    if case["dtype"] == "f32" and _decisions(case) > 2e6:
+        # Decisions at ties that 32 bits cannot tell apart are certain here, and each moves the gradient by more than
+        # all rounding: it has no 64-bit value to be compared with (the smaller cases have one).
+        out["momentum"] = None
+    if not _gradient_told(case):
+        del out["momentum"]
+    return out
