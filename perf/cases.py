@@ -174,7 +174,8 @@ def draw(rng):
             case = dict(kind="round", model="resnet18", dtype=rng.choice(["f32", "bf16"]), C=rng.randint(1, 4),
                         B=_log(rng, 12, 64))
         elif u < 0.85:
-            case = dict(kind="round", model=rng.choice(["ragged", "ragged_norm", "stage"]), dtype=rng.choice(["f32", "bf16"]),
+            case = dict(kind="round", model=rng.choice(["ragged", "ragged_norm", "stage"]),
+                        dtype=rng.choice(["f32", "bf16"]),
                         C=rng.randint(1, 6), B=_log(rng, 5, 100), side=4 * rng.randint(2, 5), w1=8 * rng.randint(1, 4),
                         w2=8 * rng.randint(1, 8), w3=8 * rng.randint(2, 24), classes=rng.randint(2, 16))
         elif u < 0.95:
