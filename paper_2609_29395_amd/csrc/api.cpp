@@ -322,6 +322,11 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
   p.off_x = take((size_t)p.esz * p.max_window * p.x_rs);
   size_t part = 0, npart = 0;
   std::vector<const LayerInfo *> split_layers;
+  struct SplitPlan {
+    LayerInfo *l;
+    int M, kt, splits, most;  // pixels, k tile, split count wanted, and the count it may always take
+  };
+  std::vector<SplitPlan> split_plans;
   // split-K over pixels for a weight gradient of M pixels per replica with
   // Ci_eff columns per tap (taps 9, or 1 on im2col rows)
   auto plan_wgrad = [&](LayerInfo &l, int M, int Ci_eff, int taps, int Hh, int Ww) {
@@ -369,16 +374,24 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
       splits = (int)std::min<int64_t>(std::max(1, nkt / 4), (target + tiles - 1) / tiles);
       splits = std::max(1, splits);
     }
-    const int per = (nkt + splits - 1) / splits;
-    l.chunk = per * kt;
-    l.splits = (M + l.chunk - 1) / l.chunk;
-    if (l.splits > 1) {  // its own partials, 16-byte aligned, weights then biases
-      l.part_off = part;
-      part = (part + (size_t)l.splits * C * l.nw + 3) / 4 * 4;
-      l.dbpart_off = part;
-      part = (part + (size_t)l.splits * C * l.Co + 3) / 4 * 4;
-      split_layers.push_back(&l);
+    int want = splits;
+    if (p.dtype == GCPSL_F32 && wgrad_f32_halo(l.Co, Ci_eff, Ww, taps)) {
+      // two workgroups per CU: on 4 replicas of 64 examples, 128 -> 128 at
+      // 16 x 16 takes 118 / 87 / 84 / 84 us with 256 / 512 / 768 / 1024
+      // workgroups, 64 -> 64 at 32 x 32 112 / 106 / 86 with 256 / 384 / 512
+      const int64_t tiles = wgrad_f32_tiles(l.Co, Ci_eff, Ww, taps) * C;
+      want = (int)std::max<int64_t>(1, std::min<int64_t>(std::max(1, nkt / 4), (512 + tiles - 1) / tiles));
     }
+    split_plans.push_back(SplitPlan{&l, M, kt, want, splits});
+  };
+  // chunks of whole k tiles; partial floats of a split count
+  auto split_chunk = [](const SplitPlan &sp, int splits) {
+    const int nkt = (sp.M + sp.kt - 1) / sp.kt;
+    return (nkt + splits - 1) / splits * sp.kt;
+  };
+  auto split_floats = [&](const SplitPlan &sp, int splits) {
+    const int chunk = split_chunk(sp, splits), n_ = (sp.M + chunk - 1) / chunk;
+    return n_ > 1 ? (int64_t)n_ * C * (sp.l->nw + sp.l->Co) : 0;
   };
   // kernels address one replica's tensors with 32-bit byte offsets and mark
   // invalid lanes with offset 2^31
@@ -526,6 +539,28 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
       }
       const bool col = i == 0 && p.col0;
       plan_wgrad(l, B * l.H * l.W, col ? p.Kc : l.Ci, col ? 1 : 9, l.H, l.W);
+    }
+  }
+  {
+    // Split counts beyond the general rule only while the partials together
+    // stay within what that rule needs, so that the workspace does not grow.
+    int64_t wanted = 0, allowed = 0;
+    for (const SplitPlan &sp : split_plans) {
+      wanted += split_floats(sp, sp.splits);
+      allowed += split_floats(sp, sp.most);
+    }
+    for (SplitPlan &sp : split_plans) {
+      if (wanted > allowed) sp.splits = std::min(sp.splits, sp.most);
+      LayerInfo &l = *sp.l;
+      l.chunk = split_chunk(sp, sp.splits);
+      l.splits = (sp.M + l.chunk - 1) / l.chunk;
+      if (l.splits > 1) {  // its own partials, 16-byte aligned, weights then biases
+        l.part_off = part;
+        part = (part + (size_t)l.splits * C * l.nw + 3) / 4 * 4;
+        l.dbpart_off = part;
+        part = (part + (size_t)l.splits * C * l.Co + 3) / 4 * 4;
+        split_layers.push_back(&l);
+      }
     }
   }
   p.off_dh = take(sizeof(float) * (size_t)C * B * p.Ch_head);

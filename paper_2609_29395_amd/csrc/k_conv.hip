@@ -9,13 +9,13 @@
 // BM x BN output tile of one replica; replicas are folded into the linear
 // workgroup index, so one launch covers all C clusters.
 //
-// Tiles are staged through LDS in "k-contiguous" rows of 128 bytes (64 bf16
-// or 32 fp32 k values) plus 16 bytes of padding, double buffered with one
-// barrier per k tile.  4 waves in a 2x2 layout each own a (BM/2) x (BN/2)
-// sub-tile of 16x16 MFMA blocks.  A lane's operand fragment is 8 consecutive
-// k values of one row: one v_mfma_f32_16x16x32_bf16, or eight
-// v_mfma_f32_16x16x4_f32 (lane group g feeds k = 8g + j to the j-th), so the
-// fp32 and bf16 paths share the LDS layout and the tile loop.
+// These are the general bf16 kernels (k_conv_f32.hip has the fp32 ones, and
+// k_conv_lds.hip, k_conv_img.hip and k_wgrad_lds.hip the bf16 shapes they
+// take).  Tiles are staged through LDS in "k-contiguous" rows of 128 bytes
+// (64 bf16 k values) plus 16 bytes of padding, double buffered with one
+// barrier per k tile.  The waves each own a sub-tile of 16x16 MFMA blocks.  A
+// lane's operand fragment is 8 consecutive k values of one row: one
+// v_mfma_f32_16x16x32_bf16.
 #include "runtime.h"
 
 namespace {
@@ -25,27 +25,14 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 template <typename T> struct Frag;
 template <> struct Frag<bf16_t> { uint4 q; };
-template <> struct Frag<float> { float v[8]; };
 
 __device__ __forceinline__ void load_frag(Frag<bf16_t> &f, const bf16_t *p) {
   f.q = *reinterpret_cast<const uint4 *>(p);
-}
-__device__ __forceinline__ void load_frag(Frag<float> &f, const float *p) {
-  const uint4 x = *reinterpret_cast<const uint4 *>(p);
-  const uint4 y = *reinterpret_cast<const uint4 *>(p + 4);
-  f.v[0] = __uint_as_float(x.x); f.v[1] = __uint_as_float(x.y);
-  f.v[2] = __uint_as_float(x.z); f.v[3] = __uint_as_float(x.w);
-  f.v[4] = __uint_as_float(y.x); f.v[5] = __uint_as_float(y.y);
-  f.v[6] = __uint_as_float(y.z); f.v[7] = __uint_as_float(y.w);
 }
 
 __device__ __forceinline__ void mma(f32x4_t &acc, const Frag<bf16_t> &a, const Frag<bf16_t> &b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a.q),
                                                 __builtin_bit_cast(bf16x8_t, b.q), acc, 0, 0, 0);
-}
-__device__ __forceinline__ void mma(f32x4_t &acc, const Frag<float> &a, const Frag<float> &b) {
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j], b.v[j], acc, 0, 0, 0);
 }
 
 template <typename T> struct Pack {
@@ -334,15 +321,6 @@ __device__ __forceinline__ void transpose_block<bf16_t>(const uint4 (&in)[8], ui
   }
 }
 
-// 4 pixels x 4 fp32 channels -> 4 channels x 4 pixels.
-template <>
-__device__ __forceinline__ void transpose_block<float>(const uint4 (&in)[4], uint4 (&out)[4]) {
-  out[0] = make_uint4(in[0].x, in[1].x, in[2].x, in[3].x);
-  out[1] = make_uint4(in[0].y, in[1].y, in[2].y, in[3].y);
-  out[2] = make_uint4(in[0].z, in[1].z, in[2].z, in[3].z);
-  out[3] = make_uint4(in[0].w, in[1].w, in[2].w, in[3].w);
-}
-
 // Transpose a VEC x VEC (pixel x channel) block and store channel row q at
 // dst + q * ldr, one row at a time (keeps few registers live).
 template <typename T>
@@ -363,14 +341,6 @@ __device__ __forceinline__ void store_transposed<bf16_t>(const uint4 (&in)[8], b
     }
     *reinterpret_cast<uint4 *>(dst + q * ldr) = make_uint4(o[0], o[1], o[2], o[3]);
   }
-}
-
-template <>
-__device__ __forceinline__ void store_transposed<float>(const uint4 (&in)[4], float *dst, int ldr) {
-  uint4 o[4];
-  transpose_block<float>(in, o);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) *reinterpret_cast<uint4 *>(dst + q * ldr) = o[q];
 }
 
 template <typename T, int BM, int BN, int WM, int WN, bool VB>
@@ -638,17 +608,11 @@ hipError_t run_conv(const ConvArgs &a, hipStream_t s, std::string *label) {
 
 template <typename T, bool VA>
 hipError_t pick_conv(const ConvArgs &a, hipStream_t s, std::string *label) {
-  // 16-bit tiles run 8 waves (4 per SIMD at two workgroups per CU): the extra
-  // resident waves hide LDS and global latency better than larger wave tiles.
-  if constexpr (sizeof(T) == 2) {
-    if (a.N > 64) return run_conv<T, 128, 128, VA, 4, 2, 1, 128, 4>(a, s, label);
-    if (a.N > 32) return run_conv<T, 128, 64, VA, 4, 2, 1, 128, 4>(a, s, label);
-    return run_conv<T, 128, 32, VA, 4, 2, 1, 128, 4>(a, s, label);
-  } else {
-    if (a.N > 64) return run_conv<T, 128, 128, VA>(a, s, label);
-    if (a.N > 32) return run_conv<T, 128, 64, VA>(a, s, label);
-    return run_conv<T, 128, 32, VA>(a, s, label);
-  }
+  // 8 waves (4 per SIMD at two workgroups per CU): the extra resident waves
+  // hide LDS and global latency better than larger wave tiles.
+  if (a.N > 64) return run_conv<T, 128, 128, VA, 4, 2, 1, 128, 4>(a, s, label);
+  if (a.N > 32) return run_conv<T, 128, 64, VA, 4, 2, 1, 128, 4>(a, s, label);
+  return run_conv<T, 128, 32, VA, 4, 2, 1, 128, 4>(a, s, label);
 }
 
 template <typename T, int BM, int BN, bool VB, int WM = 2, int WN = 2>
@@ -709,7 +673,7 @@ hipError_t launch_conv(int dtype, const ConvArgs &a, hipStream_t s, std::string 
   if (conv_lds_ok(dtype, a)) return launch_conv_lds(a, s, label);
   if (dtype == GCPSL_BF16)
     return (a.Csrc % 8 == 0) ? pick_conv<bf16_t, true>(a, s, label) : pick_conv<bf16_t, false>(a, s, label);
-  return (a.Csrc % 4 == 0) ? pick_conv<float, true>(a, s, label) : pick_conv<float, false>(a, s, label);
+  return launch_conv_f32(a, s, label);
 }
 
 hipError_t launch_wgrad(int dtype, const WgradArgs &a, hipStream_t s, std::string *label) {
@@ -727,6 +691,5 @@ hipError_t launch_wgrad(int dtype, const WgradArgs &a, hipStream_t s, std::strin
   if (dtype == GCPSL_BF16)
     return (a.Ci % 8 == 0 && (a.taps == 1 || a.W % 8 == 0)) ? pick_wgrad<bf16_t, true>(a, s, label)
                                                             : pick_wgrad<bf16_t, false>(a, s, label);
-  return (a.Ci % 4 == 0 && (a.taps == 1 || a.W % 4 == 0)) ? pick_wgrad<float, true>(a, s, label)
-                                                          : pick_wgrad<float, false>(a, s, label);
+  return launch_wgrad_f32(a, s, label);
 }

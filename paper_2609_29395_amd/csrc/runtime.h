@@ -99,6 +99,13 @@ struct WgradArgs {
 // label (optional) receives the kernel instantiation chosen for the shape.
 hipError_t launch_conv(int dtype, const ConvArgs &a, hipStream_t s, std::string *label = nullptr);
 hipError_t launch_wgrad(int dtype, const WgradArgs &a, hipStream_t s, std::string *label = nullptr);
+// fp32 layers on the bf16 matrix cores, every operand split into three bf16
+// parts (k_conv_f32.hip): channels in multiples of 4 (8 with 9 taps),
+// chunk % 32 == 0.
+hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s, std::string *label);
+hipError_t launch_wgrad_f32(const WgradArgs &a, hipStream_t s, std::string *label);
+bool wgrad_f32_halo(int Co, int Ci, int W, int taps);
+int64_t wgrad_f32_tiles(int Co, int Ci, int W, int taps);  // workgroups of one split of one replica
 int wgrad_k_tile(int dtype);
 // bf16 weight gradient with LDS-direct tile copies and transposing LDS reads
 // (k_wgrad_lds.hip): usable when wgrad_lds_ok; needs chunk % 64 == 0.

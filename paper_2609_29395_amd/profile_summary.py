@@ -58,6 +58,16 @@ def kernel_label(name: str) -> str:
         t = "bf16" if m.group(1) == "unsigned short" else "f32"
         w = int(m.group(4)) * int(m.group(5))
         return f"conv_wgrad<{t},{m.group(2)}x{m.group(3)},w{w},{'vec' if m.group(6) == 'true' else 'gather'}>"
+    m = re.search(r"conv_f32_(halo_)?kernel<(\d+), (\d+), (\d+), (\d+), (\d)", name)
+    if m:  # fp32 on the bf16 matrix cores
+        kind = "conv_fwd" if m.group(6) == "0" else "conv_dgrad"
+        return (f"{kind}<f32,{m.group(2)}x{m.group(3)},w{int(m.group(4)) * int(m.group(5))},"
+                f"{'halo,' if m.group(1) else ''}split>")
+    if re.search(r"wgrad_f32_halo_kernel\b", name):
+        return "conv_wgrad<f32,64x288,w4,halo,split>"
+    m = re.search(r"wgrad_f32_kernel<(\d+), (\d+), (\d+), (\d+)", name)
+    if m:
+        return f"conv_wgrad<f32,{m.group(1)}x{m.group(2)},w{int(m.group(3)) * int(m.group(4))},split>"
     # (an optional last flag marks the halo forward that also writes the image means)
     m = re.search(r"conv_lds_kernel<(\d+), (\d+), (\d+), (\d+), (\d), (true|false)(, (true|false))?"
                   r"(, (true|false))?(, (\d))?>", name)
@@ -106,6 +116,8 @@ SHARED_HEADERS = ("common.h",)  # device helpers every kernel source includes
 
 def kernel_source(label: str) -> str:
     """The source file that holds the kernel a timing label names."""
+    if label.startswith("conv_") and label.endswith(",split>"):
+        return "k_conv_f32.hip"
     if label.startswith("conv_wgrad<") and label.endswith((",lds>", ",halo>", ",img>", ",col>", ",img3>", ",pool>")):
         return "k_wgrad_lds.hip"
     if label.startswith("conv_") and label.endswith((",lds>", ",halo>", ",halo1>")):

@@ -1,0 +1,130 @@
+"""The fp32 convolutions on the bf16 matrix cores (k_conv_f32.hip): every tile
+and both stagings at the sizes where they can go wrong, against the oracle,
+and sums with operands that have no finite three-way split."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from gcpsl_inputs import get_config  # noqa: E402
+from paper_2609_29395_amd import gcpsl  # noqa: E402
+from test_gpu_parity import check_run, matched_run  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _net(w1, w2, w3, classes=4):
+    return [("conv", 3, w1, False), ("conv", w1, w2, False), ("conv", w2, w3, False), ("conv", w3, w3, True),
+            ("avgpool",), ("linear", w3, classes)]
+
+
+# image side (W beside the halo kernels' 32-pixel limit), batch and widths:
+# 8 and 24 channels (per-tap staging), 32 and 40 (halo, a ragged second
+# block), 64 / 72 / 136 (tile edges in N); M tails of every tile; enough
+# workgroups for the 256- and 128-pixel tiles, and too few
+@pytest.mark.parametrize("side,B,C,widths", [
+    (4, 3, 2, (8, 32, 40)), (4, 24, 2, (32, 136, 72)), (5, 7, 3, (24, 40, 64)), (7, 5, 1, (40, 72, 136)),
+    (16, 9, 2, (32, 64, 136)), (32, 3, 1, (32, 64, 32)), (33, 2, 2, (32, 40, 8)), (16, 64, 4, (8, 32, 128)),
+])
+def test_round_against_the_oracle(side, B, C, widths):
+    cfg = get_config("tiny", H=side, W=side, B=B, C=C, K=8 * C, N_ex=4 * max(C * B, 16), layers=_net(*widths), cut=2,
+                     momentum=0.9, F=0, T=1)
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)
+
+
+def _round(images, layers, side, change=None):
+    """One round of one cluster on `images` (all of them, one batch): act0,
+    act1, grad, the batch's example order, labels and parameters."""
+    B = len(images)
+    rng = np.random.default_rng(3)
+    labels = rng.integers(0, 4, B).astype(np.int32)
+    shapes = []
+    for s in layers:
+        if s[0] == "conv":
+            shapes += [(s[2], 3, 3, s[1]), (s[2],)]
+        elif s[0] == "linear":
+            shapes += [(s[2], s[1]), (s[2],)]
+    theta = [rng.uniform(-0.3, 0.3, s).astype(np.float32) for s in shapes]
+    if change:
+        change(theta)
+    cfg = dict(K=1, C=1, B=B, L=4, H=side, W=side, Cin=3, N_ex=B, layers=layers, cut=1, dtype="f32", lr=0.0,
+               momentum=0.0, seed=0)
+    ctx = gcpsl.Context(cfg, images, labels, np.zeros(B, np.int32), np.zeros(1, np.int32),
+                        np.concatenate([t.reshape(-1) for t in theta]), max_steps=1)
+    ctx.sample(0)
+    ctx.step(0)
+    torch.cuda.synchronize()
+    idx = ctx.tensor("idx").cpu().numpy()
+    acts = [ctx.tensor(f"act{i}").cpu().numpy().reshape(B, side, side, -1) for i in range(2)]
+    return acts, ctx.tensor("grad").cpu().numpy(), idx, labels, theta
+
+
+def _conv(x, w, b):
+    """ReLU(conv) in float64 (a product of an infinity and a padding zero is
+    NaN, as on the GPU, and ReLU turns NaN into 0)."""
+    n, h, ww, c = x.shape
+    p = np.zeros((n, h + 2, ww + 2, c))
+    p[:, 1:-1, 1:-1] = x
+    with np.errstate(invalid="ignore", over="ignore"):
+        z = sum(p[:, r:r + h, s:s + ww, None, :] * w[:, r, s].astype(np.float64) for r in range(3) for s in range(3))
+        z = z.sum(-1) + b
+    return np.where(z > 0, z, 0.0)
+
+
+LAYERS = [("conv", 3, 40, False), ("conv", 40, 40, False), ("avgpool",), ("linear", 40, 4)]
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_infinities_and_nan_pass_as_in_fp32(value):
+    """An infinity has no finite split: the tiles that hold one are summed in
+    plain fp32 (image layer: per-tap staging; second layer: halo staging)."""
+    side = 8
+    images = np.random.default_rng(1).standard_normal((6, side, side, 3)).astype(np.float32)
+    images[2, 3, 4, 1] = value
+    (a0, a1), _, idx, _, th = _round(images, LAYERS, side)
+    w0 = _conv(images[idx].astype(np.float64), th[0], th[1])
+    # the second layer from the GPU's own first one
+    w1 = _conv(a0.astype(np.float64), th[2], th[3])
+    for got, want in ((a0, w0), (a1, w1)):
+        inf = np.isinf(want)
+        assert np.array_equal(np.isinf(got), inf) and not np.isnan(got).any()
+        assert np.allclose(got[~inf], want[~inf], rtol=1e-5, atol=1e-5)
+    assert np.isinf(a0).any() == (not np.isnan(value))
+
+
+def test_values_that_round_to_infinity_in_bf16():
+    """Finite fp32 values above the largest bf16 (their first part rounds to
+    infinity) as image, as activation and in the weight gradient: everything
+    stays finite and right."""
+    side, big = 8, np.float32(3.4e38)
+    images = np.random.default_rng(2).standard_normal((6, side, side, 3)).astype(np.float32)
+    images[1, 2, 2, 0] = big
+
+    def change(th):  # the pixel passes the first layer nearly unscaled; the second and the head scale it down
+        th[0][::2, 1, 1, 0] = 0.9999
+        th[2] *= np.float32(1e-30)
+        th[4] *= np.float32(1e-7)
+
+    (a0, a1), grad, idx, labels, th = _round(images, LAYERS, side, change)
+    assert np.isfinite(a0).all() and np.isfinite(a1).all() and a0.max() > 3.39e38
+    assert np.allclose(a0, _conv(images[idx].astype(np.float64), th[0], th[1]), rtol=1e-5, atol=1e-5)
+    # (360 products of up to 3.4e8 cancel: an element's bound is 360 x 2^-24 of their magnitude)
+    w1 = _conv(a0.astype(np.float64), th[2], th[3])
+    assert np.abs(a1 - w1).max() <= 360 * 2.0**-24 * 3.4e8 and np.linalg.norm(a1 - w1) <= 1e-6 * np.linalg.norm(w1)
+    # dW of the second conv from the GPU's own activations
+    z = a1.astype(np.float64).mean((1, 2)) @ th[4].astype(np.float64).T + th[5]
+    p = np.exp(z - z.max(1, keepdims=True))
+    p /= p.sum(1, keepdims=True)
+    p[np.arange(6), labels[idx]] -= 1
+    g = (p / 6 @ th[4])[:, None, None] / side**2 * (a1 > 0)
+    pad = np.zeros((6, side + 2, side + 2, 40))
+    pad[:, 1:-1, 1:-1] = a0
+    want = np.stack([[np.einsum("nhwo,nhwc->oc", g, pad[:, r:r + side, s:s + side]) for s in range(3)]
+                     for r in range(3)])  # [r][s][co][ci]
+    o = th[0].size + th[1].size
+    got = grad[o:o + th[2].size].reshape(40, 3, 3, 40).transpose(1, 2, 0, 3)
+    assert np.isfinite(got).all() and np.abs(want).max() > 1e25
+    assert np.linalg.norm((got - want) / 1e25) <= 1e-4 * np.linalg.norm(want / 1e25)

@@ -50,6 +50,11 @@ def test_image_layer_labels():
     assert ps.kernel_label(ns + "wgrad_img_kernel<3, true>(WgradArgs)") == "conv_wgrad<bf16,64x288,w8,img,pool>"
     assert ps.kernel_label(ns + "conv_img_pool_kernel<64>(ConvArgs, int, int)") == \
         "conv_fwd<bf16,512x64x288,w8,img,pool>"
+    assert ps.kernel_label(ns + "conv_f32_halo_kernel<128, 64, 4, 2, 0, 4>(ConvArgs)") == \
+        "conv_fwd<f32,128x64,w8,halo,split>"
+    assert ps.kernel_label(ns + "conv_f32_kernel<64, 64, 2, 2, 1, 4>(ConvArgs)") == "conv_dgrad<f32,64x64,w4,split>"
+    assert ps.kernel_label(ns + "wgrad_f32_halo_kernel(WgradArgs)") == "conv_wgrad<f32,64x288,w4,halo,split>"
+    assert ps.kernel_label(ns + "wgrad_f32_kernel<128, 64, 2, 2, 2>(WgradArgs)") == "conv_wgrad<f32,128x64,w4,split>"
     assert ps.kernel_label(ns + "conv_img_dgrad_kernel(ConvArgs, int, int)") == "conv_dgrad<bf16,256x32x576,w8,img,pool>"
 
 
@@ -65,6 +70,9 @@ def test_image_layer_labels():
     ("conv_fwd<bf16,512x64x288,w8,img,pool>", "k_conv_img.hip"),
     ("conv_dgrad<bf16,256x32x576,w8,img,pool>", "k_conv_img.hip"),
     ("conv_fwd<f32,128x128x32,w4,vec>", "k_conv.hip"),
+    ("conv_fwd<f32,128x64,w8,halo,split>", "k_conv_f32.hip"),
+    ("conv_dgrad<f32,64x64,w4,split>", "k_conv_f32.hip"),
+    ("conv_wgrad<f32,64x288,w4,halo,split>", "k_conv_f32.hip"),
     ("sgd", "k_misc.hip"),
     ("fuse", "k_misc.hip"),
     ("chan_reduce", "k_norm.hip"),
