@@ -27,8 +27,10 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-// Pixels per chunk of a channel reduction over px pixels of each of C
-// replicas: halved from 256 down to 16 until there are about 2048 chunks in
+// Pixels per chunk of a channel reduction over px pixels of each of the
+// context's C replicas (not of a launch's slots: the partials' buffer is sized
+// for it, and a replica's sums must not depend on who shares its launch):
+// halved from 256 down to 16 until there are about 2048 chunks in
 // all, so that small late-stage tensors still spread over the chip.
 int norm_chunk(int64_t px, int C) {
   int ch = 256;
@@ -995,7 +997,7 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
     na.state = d.norm_state;
     na.P = p.P; na.g_off = l.w_off; na.b_off = l.b_off; na.S = p.S; na.st_off = l.st_off; na.z_rs = l.act_rs;
     na.Bt = B; na.H = l.H; na.W = l.W; na.Ch = l.Co; na.groups = l.groups; na.nstat = l.nstat;
-    na.chunk_px = norm_chunk((int64_t)B * l.H * l.W, C);
+    na.chunk_px = norm_chunk((int64_t)B * l.H * l.W, p.C);
     na.chunks = (int)(((int64_t)B * l.H * l.W + na.chunk_px - 1) / na.chunk_px);
     na.C = C;
     na.rmap = rmap;
@@ -1019,7 +1021,7 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
     na.P = p.P; na.g_off = nl.w_off; na.b_off = nl.b_off; na.S = p.S; na.st_off = nl.st_off;
     na.z_rs = (int64_t)B * nl.H * nl.W * nl.Co;
     na.Bt = B; na.H = nl.H; na.W = nl.W; na.Ch = nl.Co; na.groups = nl.groups; na.nstat = nl.nstat;
-    na.chunk_px = norm_chunk((int64_t)B * nl.H * nl.W, C);
+    na.chunk_px = norm_chunk((int64_t)B * nl.H * nl.W, p.C);
     na.chunks = (int)(((int64_t)B * nl.H * nl.W + na.chunk_px - 1) / na.chunk_px);
     na.C = C;
     na.rmap = rmap;
