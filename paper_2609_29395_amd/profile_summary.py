@@ -126,7 +126,8 @@ def kernel_source(label: str) -> str:
         return "k_conv_img.hip"
     if label.startswith("conv_"):
         return "k_conv.hip"
-    if label in ("chan_reduce", "chan_finish", "group_reduce", "norm_apply_fwd", "norm_apply_bwd") or \
+    if label in ("chan_reduce", "chan_finish", "group_fwd", "group_bwd", "batch_norm", "group_reduce",
+                 "norm_apply_fwd", "norm_apply_bwd") or \
             label.startswith(("batchnorm", "groupnorm")):
         return "k_norm.hip"
     if label in ("im2col", "zero_insert"):

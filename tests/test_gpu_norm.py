@@ -28,3 +28,22 @@ def test_serial_clusters_of_large_norm_layers_bit_for_bit(dtype):
         ctx.close()
     for a, b in zip(*out):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+# group norm: examples held with 256 and 512 threads, and read again (32 x 32
+# x 72 channels); 3 vectors per pixel (idle lanes); two channels per group and
+# one group; batch norm: one launch held and read twice, three launches, one
+# and two vectors per workgroup
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("side,B,C,w1,g1,w2,g2,w3", [
+    (5, 7, 2, 8, 4, 24, 1, 40), (9, 3, 1, 24, 3, 64, 32, 8), (16, 5, 2, 64, 32, 128, 32, 16), (32, 2, 1, 72, 9, 8, 2, 24),
+    (16, 33, 2, 8, 2, 16, 4, 136), (32, 9, 1, 8, 4, 8, 1, 8), (3, 5, 16, 8, 2, 16, 4, 256),
+])
+def test_norm_round_against_the_oracle(dtype, side, B, C, w1, g1, w2, g2, w3):
+    from test_gpu_parity import check_run, matched_run
+    layers = [("conv", 3, w1, False), ("gnorm", w1, g1), ("conv", w1, w2, False), ("gnorm", w2, g2),
+              ("conv", w2, w3, False), ("bnorm", w3), ("avgpool",), ("linear", w3, 4)]
+    cfg = get_config("tiny", H=side, W=side, B=B, C=C, K=8 * C, N_ex=4 * max(C * B, 16), layers=layers, cut=4,
+                     momentum=0.9, F=0, T=1, dtype=dtype)
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)

@@ -78,6 +78,8 @@ def test_image_layer_labels():
     ("chan_reduce", "k_norm.hip"),
     ("norm_apply_bwd", "k_norm.hip"),
     ("group_reduce", "k_norm.hip"),
+    ("group_bwd", "k_norm.hip"),
+    ("batch_norm", "k_norm.hip"),
     ("im2col", "k_block.hip"),
     ("zero_insert", "k_block.hip"),
 ])
