@@ -50,7 +50,7 @@ constexpr int ROW = BK * 2;  // bytes per LDS row
 constexpr uint32_t kOob = 0x80000000u;
 constexpr int kBufferFlags = 0x00020000;
 
-template <int BM_, int BN, int WM, int WN, int PFO = 0> struct Cfg {
+template <int BM_, int BN, int WM, int WN, int PFO = 0, int NST = 2> struct Cfg {
   static constexpr int BM = BM_, BN_ = BN;
   static constexpr int NW = WM * WN, NTHR = 64 * NW;  // waves, threads
   static constexpr int A_BYTES = BM * ROW, B_BYTES = BN * ROW;
@@ -69,7 +69,7 @@ template <int BM_, int BN, int WM, int WN, int PFO = 0> struct Cfg {
   static constexpr bool EP_SWZ = WNW == 64;
   static constexpr int EP_LD = EP_SWZ ? WNW : WNW + 4;
   static constexpr int EP_BYTES = NW * 16 * PF * EP_LD * 4;
-  static constexpr int LDS_BYTES = 2 * STAGE > EP_BYTES ? 2 * STAGE : EP_BYTES;
+  static constexpr int LDS_BYTES = NST * STAGE > EP_BYTES ? NST * STAGE : EP_BYTES;
   static_assert(NW == 8 || NW == 16, "8 or 16 waves");
   static_assert(SA * NTHR * 16 == A_BYTES && B_BYTES % 1024 == 0, "copies must tile the stage");
   static_assert(TM % PF == 0 && TM % 2 == 0 && TN >= 1, "wave tile: whole epilogue passes, two halves per k group");
@@ -139,6 +139,26 @@ __device__ __forceinline__ void read_frags_seq(u32x4 (&f)[T], uint32_t addr, std
 template <int T, int START = 0, int STRIDE = 2048>
 __device__ __forceinline__ void read_frags(u32x4 (&f)[T], uint32_t addr) {
   read_frags_seq<T, START, STRIDE>(f, addr, std::make_integer_sequence<int, T>{});
+}
+
+// T fragments 16 rows apart from byte OFF on, and the wait that leaves the N
+// newest LDS reads in flight (LDS reads return in order) and marks the older
+// fragments as produced.
+template <int OFF, int T, int... I>
+__device__ __forceinline__ void read_at_seq(u32x4 (&f)[T], uint32_t addr, std::integer_sequence<int, I...>) {
+  (read_frag<OFF + I * 2048>(f[I], addr), ...);
+}
+template <int OFF, int T>
+__device__ __forceinline__ void read_at(u32x4 (&f)[T], uint32_t addr) {
+  read_at_seq<OFF, T>(f, addr, std::make_integer_sequence<int, T>{});
+}
+template <int N, int TA, int TB>
+__device__ __forceinline__ void wait_older(u32x4 (&x)[TA], u32x4 (&w)[TB]) {
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
+#pragma unroll
+  for (int t = 0; t < TA; ++t) asm volatile("" : "+v"(x[t]));
+#pragma unroll
+  for (int t = 0; t < TB; ++t) asm volatile("" : "+v"(w[t]));
 }
 
 // Wait for every outstanding LDS read, then mark the fragments as produced
@@ -214,6 +234,26 @@ __device__ __forceinline__ void issue_tile(int kt, char *stage0, int wave, const
                                                boff[q] == kOob ? kOob : boff[q] + kb, 0, 0, 0);
 }
 
+// Unrolled loop: the copies of the tile at place U of a group (nine taps of a
+// channel block, three tiles of a one-tap product) whose first column is byte
+// c of a pixel's channels, into stage U % 3; aoff: this thread's pixel offsets
+// for the tile's tap.
+template <typename CF, bool TAPS1, int U>
+__device__ __forceinline__ void issue_unrolled(char *stage0, const ConvArgs &a, const void *src, const void *wt,
+                                               const uint32_t *aoff, const uint32_t *boff, uint32_t c) {
+  const __amdgpu_buffer_rsrc_t rsa = rsrc(src, (uint32_t)(a.src_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsb = rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
+  char *sa = stage0 + (U % 3) * CF::STAGE;
+  const uint32_t ca = TAPS1 ? c + U * ROW : c, cw = TAPS1 ? ca : c + (uint32_t)(U * a.Csrc * 2);
+#pragma unroll
+  for (int q = 0; q < CF::SA; ++q)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, LDS_PTR(sa + q * CF::NTHR * 16), 16, aoff[q], ca, 0, 0);
+#pragma unroll
+  for (int q = 0; q < CF::SB; ++q)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, LDS_PTR(sa + CF::A_BYTES + q * CF::NTHR * 16), 16, boff[q], cw, 0,
+                                             0);
+}
+
 // Halo mode: piece q of channel block cb's halo image into buffer cb % HB
 // (hoff: this thread's source offset within the image, -1 for the zero
 // border); the last piece covers only the first waves.
@@ -254,12 +294,22 @@ __device__ __forceinline__ void issue_weights(int kt, char *smem, int wave, cons
 
 // (one halo buffer: at most 128 registers, so that two 8-wave workgroups
 // share a CU)
-template <int BM, int BN, int WM, int WN, int EPI, bool TAPS1, bool HALO = false, bool AVG = false, int HB = 2>
+//
+// UNROLL (whole 64-channel blocks): three stages, the copies of a tile issued
+// two tiles ahead, and the k loop unrolled over the nine taps (three k tiles
+// of a one-tap product), so that a tile's stage, tap and fragment offsets are
+// constants and each thread's copy offsets per tap are kept in registers.  A
+// grid of one or two workgroups per CU has two to four waves per SIMD, too few
+// to hide the general loop's 120 instructions and two-stage copy latency per
+// tile.
+template <int BM, int BN, int WM, int WN, int EPI, bool TAPS1, bool HALO = false, bool AVG = false, int HB = 2,
+          bool UNROLL = false>
 __global__ void __launch_bounds__(64 * WM * WN, (HALO && HB == 1) ? 4 : 1)
 conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int NT) {
   // one halo buffer: the two-pass epilogue keeps the staging within the
   // k loop's 73 KB
-  using CF = Cfg<BM, BN, WM, WN, (HALO && HB == 1) ? 2 : 0>;
+  using CF = Cfg<BM, BN, WM, WN, ((HALO && HB == 1) || UNROLL) ? 2 : 0, UNROLL ? 3 : 2>;
+  static_assert(!UNROLL || (!HALO && BM / WM == 32 && CF::SB * CF::NTHR * 16 == CF::B_BYTES), "unrolled loop's tile");
   static_assert(!HALO || (BM == 256 && !TAPS1 &&
                           ((BN == 256 && (WM == 4 || WM == 2) && WN == 4 && HB == 2) ||
                            (BN == 64 && WM == 8 && WN == 2 && HB == 2) ||
@@ -378,9 +428,71 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) issue_halo_piece<NTHR, HB>(q, 0, smem, wave, a, src, img_off, hoff[q]);
     issue_weights<CF, TPK, HB>(0, smem, wave, a, wt, boff);
-  } else {
+  } else if constexpr (!UNROLL) {
     issue(0);
   }
+  if constexpr (UNROLL) {
+    constexpr int UN = TAPS1 ? 3 : 9, CPT = SA + SB;
+    uint32_t aoff[TAPS1 ? 1 : 9][SA];  // byte offset of this thread's copies, per tap
+#pragma unroll
+    for (int q = 0; q < SA; ++q)
+#pragma unroll
+      for (int t = 0; t < (TAPS1 ? 1 : 9); ++t) {
+        const int tap = TAPS1 ? 0 : ((t / 3 - 1) * a.W + (t % 3 - 1)) * a.Csrc;
+        aoff[t][q] = ((amask[q] >> t) & 1u) ? (uint32_t)(arowoff[q] + tap + 8 * achunk[q]) * 2u : kOob;
+      }
+    auto copy = [&](auto U, uint32_t c) {
+      constexpr int u = decltype(U)::value;
+      issue_unrolled<CF, TAPS1, u>(stage0, a, src, wt, aoff[TAPS1 ? 0 : u], boff, c);
+    };
+    const uint32_t xr[2] = {lds0 + xa[0], lds0 + xa[1]}, wr[2] = {lds0 + wa[0], lds0 + wa[1]};
+    int k0 = 0;          // first tile of the group
+    uint32_t gcol = 0u;  // and its first column (bytes)
+    constexpr uint32_t GCOL = TAPS1 ? 3 * ROW : ROW;
+    auto step = [&](auto U) {
+      constexpr int u = decltype(U)::value;
+      if (TAPS1 && k0 + u >= nk) return;
+      // tile k0 + u has landed for every wave (copies land in issue order: the
+      // next tile's may stay in flight), and every wave is done with the tile
+      // before it, whose stage takes tile k0 + u + 2
+      if ((!TAPS1 && u < 8) || k0 + u + 1 < nk)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPT) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      asm volatile("s_barrier" ::: "memory");
+      if ((!TAPS1 && u < 7) || k0 + u + 2 < nk)
+        copy(std::integral_constant<int, (u + 2) % UN>{}, gcol + (uint32_t)((u + 2) / UN) * GCOL);
+      u32x4 w0[TN], x0[TM], w1[TN], x1[TM];
+      constexpr int SO = (u % 3) * CF::STAGE;
+      read_at<SO>(w0, wr[0]);
+      read_at<SO>(x0, xr[0]);
+      read_at<SO>(w1, wr[1]);
+      read_at<SO>(x1, xr[1]);
+      wait_older<TM + TN>(x0, w0);
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w0[tn], x0[tm]);
+      __builtin_amdgcn_sched_barrier(0);
+      wait_older<0>(x1, w1);
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w1[tn], x1[tm]);
+    };
+    auto steps = [&](auto... U) { (step(U), ...); };
+    copy(std::integral_constant<int, 0>{}, 0u);
+    if (nk > 1) copy(std::integral_constant<int, 1>{}, 0u);
+    for (; k0 < nk; k0 += UN, gcol += GCOL) {
+      if constexpr (TAPS1)
+        steps(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+      else
+        steps(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{},
+              std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
+              std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{}, std::integral_constant<int, 8>{});
+    }
+  }
+  if constexpr (!UNROLL)
   for (int kt = 0; kt < nk; ++kt) {
     // own copies of tile kt have landed; after the barrier every wave's
     // have, and every wave is done with tile kt-1, whose stage is refilled
@@ -737,6 +849,11 @@ bool conv_fuses_avg(int dtype, const ConvArgs &a) {
          a.N <= 256;
 }
 
+// The unrolled k loop on 128 x 64 tiles: 8 waves of 32 x 32, three stages of 24
+// KB, two workgroups per CU.
+using UnrollCfg = Cfg<128, 64, 4, 2, 2, 3>;
+static_assert(2 * UnrollCfg::LDS_BYTES <= 160 * 1024, "two workgroups per CU");
+
 // Every instantiation is named in this (non-template) function, which is
 // what makes the compiler emit the host-side launch stubs.
 hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label) {
@@ -778,6 +895,13 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
           hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, halo_lds_of<Halo128Cfg, 1, 1>());
       if (e != hipSuccess) return e;
     }
+    for (const void *f : {reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_FWD, false, false, false, 2, true>),
+                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_FWD, true, false, false, 2, true>),
+                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, false, false, false, 2, true>),
+                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, true, false, false, 2, true>)}) {
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, UnrollCfg::LDS_BYTES);
+      if (e != hipSuccess) return e;
+    }
     CONV_LDS_ATTR(256, 256, 4, 4)
     CONV_LDS_ATTR(256, 128, 4, 2)
     CONV_LDS_ATTR(128, 64, 2, 4)
@@ -807,6 +931,15 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
     if (bn == 256 && wgs(256, 256) < 512) bn = 128;
     if (bn == 128 && wgs(256, 128) < 512) bn = 64, bm = 128;
   }
+  // 64-wide tiles over whole 64-channel blocks take the unrolled loop at any
+  // grid: on 4 replicas of 64 examples, forward / input gradient, 512 -> 512 at
+  // 4 x 4 (256 tiles) 62 / 62 -> 33 / 32 us, 256 -> 256 at 8 x 8 (512 tiles) 36 /
+  // 36 -> 27 / 26, 64 -> 64 at 32 x 32 (2048 tiles; before, 1024 of 256 x 64) 33 /
+  // 37 -> 31 / 33.  With four or six stages a workgroup has the CU to itself:
+  // the same at 256 tiles, slower beyond.  Channel counts that break a block
+  // keep the general loop, whose copies find their tap by channel.
+  const bool unroll = bn == 64 && !use_halo64 && (a.taps == 1 ? a.K : a.Csrc) % BK == 0;
+  if (unroll) bm = 128;
   int MT, NT;
   if (use_h128) grid<256, 128>(a, &MT, &NT);
   else if (bn == 256) grid<256, 256>(a, &MT, &NT);
@@ -828,6 +961,8 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
       *label = std::string(a.epi == EPI_FWD ? "conv_fwd" : "conv_dgrad") + "<bf16,256x128x64,w8,halo1>";
     else if (use_h64)
       *label = "conv_dgrad<bf16,256x64x64,w8,halo1>";
+    else if (unroll)
+      *label = std::string(a.epi == EPI_FWD ? "conv_fwd" : "conv_dgrad") + "<bf16,128x64x64,w8,unroll>";
     else
       *label = std::string(a.epi == EPI_FWD ? "conv_fwd" : "conv_dgrad") + "<bf16," + std::to_string(bm) + "x" +
                std::to_string(bn) + (use_halo64 ? "x192,w16" : "x64,w") +
@@ -872,6 +1007,15 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
     else
       hipLaunchKernelGGL((conv_lds_kernel<256, 64, 8, 2, EPI_DGRAD, false, true>), g, dim3(Halo64Cfg::NTHR),
                          (halo_lds_of<Halo64Cfg, 3>()), s, b, fw, fh, fc, MT, NT);
+    return hipGetLastError();
+  }
+  if (unroll) {
+#define CONV_LDS_UNROLL(E, T)                                                                         \
+  hipLaunchKernelGGL((conv_lds_kernel<128, 64, 4, 2, E, T, false, false, 2, true>), g, dim3(UnrollCfg::NTHR), \
+                     (UnrollCfg::LDS_BYTES), s, b, fw, fh, fc, MT, NT)
+    if (a.epi == EPI_FWD) { if (a.taps == 1) CONV_LDS_UNROLL(EPI_FWD, true); else CONV_LDS_UNROLL(EPI_FWD, false); }
+    else { if (a.taps == 1) CONV_LDS_UNROLL(EPI_DGRAD, true); else CONV_LDS_UNROLL(EPI_DGRAD, false); }
+#undef CONV_LDS_UNROLL
     return hipGetLastError();
   }
 #define CONV_LDS_GO(BM, BN, WM, WN, E, T)                                                                  \

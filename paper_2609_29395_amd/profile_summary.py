@@ -70,11 +70,11 @@ def kernel_label(name: str) -> str:
         return f"conv_wgrad<f32,{m.group(1)}x{m.group(2)},w{int(m.group(3)) * int(m.group(4))},split>"
     # (an optional last flag marks the halo forward that also writes the image means)
     m = re.search(r"conv_lds_kernel<(\d+), (\d+), (\d+), (\d+), (\d), (true|false)(, (true|false))?"
-                  r"(, (true|false))?(, (\d))?>", name)
+                  r"(, (true|false))?(, (\d))?(, (true|false))?>", name)
     if m:
         kind = "conv_fwd" if m.group(5) == "0" else "conv_dgrad"
         w = int(m.group(3)) * int(m.group(4))
-        mode = "halo" if m.group(8) == "true" else "lds"
+        mode = "halo" if m.group(8) == "true" else "unroll" if m.group(14) == "true" else "lds"
         if mode == "halo" and m.group(12) == "1":  # one halo buffer
             return f"{kind}<bf16,{m.group(1)}x{m.group(2)}x64,w{w},halo1>"
         kt = 192 if (mode == "halo" and m.group(2) == "64") else 64  # tap-row k tiles
@@ -120,7 +120,7 @@ def kernel_source(label: str) -> str:
         return "k_conv_f32.hip"
     if label.startswith("conv_wgrad<") and label.endswith((",lds>", ",halo>", ",img>", ",col>", ",img3>", ",pool>")):
         return "k_wgrad_lds.hip"
-    if label.startswith("conv_") and label.endswith((",lds>", ",halo>", ",halo1>")):
+    if label.startswith("conv_") and label.endswith((",lds>", ",unroll>", ",halo>", ",halo1>")):
         return "k_conv_lds.hip"
     if label.startswith("conv_") and label.endswith((",img>", ",col>", ",img3>", ",img,pool>")):
         return "k_conv_img.hip"

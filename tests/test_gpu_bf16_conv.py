@@ -1,0 +1,42 @@
+"""The bf16 convolutions whose k loop is unrolled over whole 64-channel blocks
+(k_conv_lds.hip, 128 x 64 tiles): the edges of its tiles and of its loop,
+against the oracle."""
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from gcpsl_inputs import get_config  # noqa: E402
+from test_gpu_parity import check_run, matched_run  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+# 3 x 3: one, two and three channel blocks; one pixel to several tiles with a
+# ragged last one; output channels that end inside a tile (72, 136); a
+# residual layer; images of one pixel and a width that is no power of two
+@pytest.mark.parametrize("side,B,C,w1,w2,w3", [
+    (1, 5, 1, 64, 64, 128), (4, 8, 2, 64, 128, 64), (5, 27, 2, 64, 72, 64), (6, 29, 3, 64, 136, 192), (12, 20, 3, 64, 64, 128),
+    (32, 2, 2, 64, 64, 64),
+])
+def test_three_by_three(side, B, C, w1, w2, w3):
+    layers = [("conv", 3, w1, False), ("conv", w1, w2, False), ("conv", w2, w3, False), ("conv", w3, w3, True),
+              ("avgpool",), ("linear", w3, 4)]
+    cfg = get_config("tiny", H=side, W=side, B=B, C=C, K=8 * C, N_ex=4 * max(C * B, 16), layers=layers, cut=2,
+                     momentum=0.9, F=0, T=1, dtype="bf16")
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)
+
+
+# strided blocks: one-tap products of one to four k tiles (projections) and of
+# nine and more (the im2col rows of the 3 x 3), with tails of the group of three
+@pytest.mark.parametrize("side,B,w1,w2,w3", [(4, 9, 64, 64, 128), (8, 5, 128, 192, 64), (12, 3, 192, 64, 72),
+                                             (4, 16, 256, 64, 128)])
+def test_strided_blocks(side, B, w1, w2, w3):
+    layers = [("conv", 3, w1, False), ("gnorm", w1, w1 // 8), ("block", w1, w2, 2, w2 // 8), ("block", w2, w3, 2, w3 // 8),
+              ("avgpool",), ("linear", w3, 4)]
+    cfg = get_config("tiny", H=side, W=side, B=B, C=2, K=16, N_ex=128, layers=layers, cut=3, momentum=0.9, F=0, T=1,
+                     dtype="bf16")
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)

@@ -35,6 +35,8 @@ def test_other_labels():
                            "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_dgrad<bf16,256x64x192,w16,halo>"
     assert ps.kernel_label("void (anonymous namespace)::conv_lds_kernel<128, 64, 2, 4, 0, false>"
                            "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_fwd<bf16,128x64x64,w8,lds>"
+    assert ps.kernel_label("void (anonymous namespace)::conv_lds_kernel<128, 64, 4, 2, 1, true, false, false, 2, true>"
+                           "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_dgrad<bf16,128x64x64,w8,unroll>"
 
 
 def test_image_layer_labels():
