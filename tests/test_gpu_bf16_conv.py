@@ -1,6 +1,6 @@
-"""The bf16 convolutions whose k loop is unrolled over whole 64-channel blocks
-(k_conv_lds.hip, 128 x 64 tiles): the edges of its tiles and of its loop,
-against the oracle."""
+"""bf16 convolutions against the oracle, at the sizes where their kernels can go
+wrong: the k loop unrolled over whole 64-channel blocks (k_conv_lds.hip, 128 x
+64 tiles) and the weight gradient of images of any width (k_conv.hip)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -37,6 +37,19 @@ def test_strided_blocks(side, B, w1, w2, w3):
     layers = [("conv", 3, w1, False), ("gnorm", w1, w1 // 8), ("block", w1, w2, 2, w2 // 8), ("block", w2, w3, 2, w3 // 8),
               ("avgpool",), ("linear", w3, 4)]
     cfg = get_config("tiny", H=side, W=side, B=B, C=2, K=16, N_ex=128, layers=layers, cut=3, momentum=0.9, F=0, T=1,
+                     dtype="bf16")
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)
+
+
+# fewer than 64 output channels on widths that are no multiple of a block's
+# eight pixels: blocks across image rows, images and the batch's end; one pixel
+# wide; column tiles of 32, 64 and 128
+@pytest.mark.parametrize("H,W,B,w1,w2,w3", [(1, 1, 9, 8, 8, 8), (4, 3, 5, 8, 16, 24), (2, 9, 11, 16, 56, 8), (5, 12, 7, 32, 40, 16),
+                                            (3, 33, 3, 24, 8, 56)])
+def test_weight_gradient_of_any_width(H, W, B, w1, w2, w3):
+    layers = [("conv", 3, w1, False), ("conv", w1, w2, False), ("conv", w2, w3, False), ("avgpool",), ("linear", w3, 4)]
+    cfg = get_config("tiny", H=H, W=W, B=B, C=2, K=16, N_ex=128, layers=layers, cut=2, momentum=0.9, F=0, T=1,
                      dtype="bf16")
     ctx, o, theta0, losses, _ = matched_run(cfg, 1)
     check_run(ctx, o, theta0, losses, cfg)
