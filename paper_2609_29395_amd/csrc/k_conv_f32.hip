@@ -365,8 +365,12 @@ conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
 // and tap (r, s) reads its fragments r W + s rows further; a lane whose tap
 // leaves the image reads a row of zeros instead.  The pixels' share of the
 // splitting falls from nine times per block to about once and a half, so the
-// stages are the weights' (one tap of the block each).
-template <int BM, int BN, int WM, int WN, int EPI, int OCC>
+// stages are the weights' (one tap of the block each).  A tap's weights are
+// loaded RD taps ahead (a ring of registers) and staged in two LDS buffers, one
+// barrier per tap: a tap of a small tile is 12 or 24 MFMAs of a wave, far less
+// than a load's latency, so the smaller tiles take RD = 3; the 256-pixel ones
+// have no registers for it.
+template <int BM, int BN, int WM, int WN, int EPI, int OCC, int RD>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
   constexpr int NTH = 64 * WM * WN, TM = BM / WM / 16, TN = BN / WN / 16;
@@ -374,7 +378,7 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
   constexpr int RP = NTH / 4;
   constexpr int HV = (HR + RP - 1) / RP, BV = (BN + RP - 1) / RP;
   __shared__ __attribute__((aligned(16))) char Xs[3 * (HR + 1) * 64];
-  __shared__ __attribute__((aligned(16))) char Ws[3 * BN * 64];
+  __shared__ __attribute__((aligned(16))) char Ws[2][3 * BN * 64];
   __shared__ int huge;
 
   const int tid = threadIdx.x;
@@ -405,7 +409,8 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
     offb[j] = (n < a.N && row < BN) ? ((uint32_t)n * (uint32_t)a.Kp + (uint32_t)(chunk * 8)) * 4u : kOob;
   }
   float top = 0.f;
-  uint4 rx[HV][2], rb[BV][2];
+  uint4 rx[HV][2], rb[RD][BV][2];  // rb[s]: the weights of tap s of the next RD
+  static_assert(9 % RD == 0, "ring");
   auto load_halo = [&](int c0) {
     const bool live = c0 + chunk * 8 < a.Csrc;  // channels come in multiples of 8
 #pragma unroll
@@ -416,13 +421,13 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
       rx[j][1] = buffer_load16(rsa, o + 16u);
     }
   };
-  auto load_w = [&](int c0, int rs) {
+  auto load_w = [&](uint4 (&q)[BV][2], int c0, int rs) {
     const bool live = c0 + chunk * 8 < a.Csrc;
 #pragma unroll
     for (int j = 0; j < BV; ++j) {
       const uint32_t o = live ? offb[j] + (uint32_t)((rs * a.Csrc + c0) * 4) : kOob;
-      rb[j][0] = buffer_load16(rsb, o);
-      rb[j][1] = buffer_load16(rsb, o + 16u);
+      q[j][0] = buffer_load16(rsb, o);
+      q[j][1] = buffer_load16(rsb, o + 16u);
     }
   };
   auto put = [&](char *dst, const uint4 (&q)[2], auto at) {
@@ -459,8 +464,11 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
   if (tid < 12) *reinterpret_cast<uint4 *>(Xs + lds_at<HR + 1>(tid >> 2, HR, tid & 3)) = make_uint4(0, 0, 0, 0);
   const int ncb = (a.Csrc + 31) / 32;
   load_halo(0);
-  load_w(0, 0);
+#pragma unroll
+  for (int s = 0; s < RD; ++s) load_w(rb[s], 0, s);
+  int buf = 0;
   for (int cb = 0; cb < ncb; ++cb) {
+    if (cb) __syncthreads();  // every wave has read the block before
 #pragma unroll
     for (int j = 0; j < HV; ++j) {
       const int row = rrow + RP * j;
@@ -468,15 +476,22 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
       if (HR % RP == 0 || row < HR) put(Xs, rx[j], [&](int k) { return lds_at<HR + 1>(k, row, chunk); });
     }
 #pragma unroll 1
-    for (int rs = 0; rs < 9; ++rs) {
+    for (int t0 = 0; t0 < 9; t0 += RD)
+#pragma unroll
+    for (int s = 0; s < RD; ++s) {
+      const int rs = t0 + s;
+      char *wb = Ws[buf];
+      buf ^= 1;
 #pragma unroll
       for (int j = 0; j < BV; ++j) {
         const int row = rrow + RP * j;
-        if (BN % RP == 0 || row < BN) put(Ws, rb[j], [&](int k) { return lds_at<BN>(k, row, chunk); });
+        if (BN % RP == 0 || row < BN) put(wb, rb[s][j], [&](int k) { return lds_at<BN>(k, row, chunk); });
       }
+      // (the other buffer's readers have passed this barrier before it is
+      // written again)
       __syncthreads();
       if (rs == 6) load_halo((cb + 1) * 32);  // (past the last block: nothing is read)
-      load_w(rs < 8 ? cb * 32 : cb * 32 + 32, rs < 8 ? rs + 1 : 0);
+      load_w(rb[s], rs < 9 - RD ? cb * 32 : cb * 32 + 32, rs < 9 - RD ? rs + RD : rs + RD - 9);
       const int r = (rs * 11) >> 5, shift = r * a.W + rs - 3 * r;
       const int row0 = wm0 + li + shift;
       const int at0 = lds_at<HR + 1>(0, row0, lg), zero = lds_at<HR + 1>(0, HR, lg);
@@ -485,7 +500,7 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int k = 0; k < 3; ++k)
-          w[j].p[k] = *reinterpret_cast<const bf16x8_t *>(Ws + lds_at<BN>(k, wn0 + j * 16 + li, lg));
+          w[j].p[k] = *reinterpret_cast<const bf16x8_t *>(wb + lds_at<BN>(k, wn0 + j * 16 + li, lg));
       // pixel fragments two at a time (fewer registers; the other waves cover the reads)
       constexpr int XB = TM > 2 ? 2 : TM;
 #pragma unroll
@@ -500,7 +515,6 @@ conv_f32_halo_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, int MT, int NT) {
         sums.add(w, x, i0);
         if (i0 + XB < TM) __builtin_amdgcn_sched_barrier(0);
       }
-      __syncthreads();
     }
   }
   if (top >= kHuge) huge = 1;
@@ -918,7 +932,7 @@ hipError_t run_conv(const ConvArgs &a, hipStream_t s, std::string *label) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int OCC>
+template <int BM, int BN, int WM, int WN, int OCC, int RD>
 hipError_t run_conv_halo(const ConvArgs &a, hipStream_t s, std::string *label) {
   const int M = a.Bt * a.H * a.W;
   const int MT = (M + BM - 1) / BM, NT = (a.N + BN - 1) / BN;
@@ -929,10 +943,10 @@ hipError_t run_conv_halo(const ConvArgs &a, hipStream_t s, std::string *label) {
              std::to_string(BN) + ",w" + std::to_string(WM * WN) + ",halo,split>";
   const dim3 threads(64 * WM * WN);
   if (a.epi == EPI_FWD)
-    hipLaunchKernelGGL((conv_f32_halo_kernel<BM, BN, WM, WN, EPI_FWD, OCC>), dim3(blocks), threads, 0, s, a, fw,
+    hipLaunchKernelGGL((conv_f32_halo_kernel<BM, BN, WM, WN, EPI_FWD, OCC, RD>), dim3(blocks), threads, 0, s, a, fw,
                        fh, MT, NT);
   else
-    hipLaunchKernelGGL((conv_f32_halo_kernel<BM, BN, WM, WN, EPI_DGRAD, OCC>), dim3(blocks), threads, 0, s, a,
+    hipLaunchKernelGGL((conv_f32_halo_kernel<BM, BN, WM, WN, EPI_DGRAD, OCC, RD>), dim3(blocks), threads, 0, s, a,
                        fw, fh, MT, NT);
   return hipGetLastError();
 }
@@ -967,18 +981,23 @@ hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s, std::string *label)
   //   1 replica,  128 -> 128 at 16 x 16    80 /  36 /  38 /  48
   //   1 replica,  512 -> 512 at 4 x 4     283 / 137 / 114 / 102
   //   4 replicas,  64 ->  64 at 32 x 32     - / 112 / 119         (162)
+  // The table is with the weights loaded one tap ahead.  Three taps ahead, the
+  // chosen tiles (forward): 256 -> 256 at 8 x 8 95 -> 92, 512 -> 512 at 4 x 4 143
+  // -> 117, 64 -> 64 at 32 x 32 103 -> 97; 1 replica, 128 -> 128 at 16 x 16 36 ->
+  // 31; 32 x 64 (3 replicas of 20 examples, 136 -> 136 at 6 x 6) 34 -> 28; 64 x 32
+  // (24 -> 8 at 12 x 12) 33 -> 27.
   // (4 x 4 images: a 128-pixel tile's taps read eight images' borders, mostly
   // zeros, so 64 pixels do better.)
   if (a.taps == 9 && a.W <= kHaloW && a.Csrc >= 32 && 45 * ((a.Csrc + 31) / 32) <= 6 * ((9 * a.Csrc + 31) / 32)) {
     if (a.N > 32) {
-      if (a.N > 64 && blocks(256, 128) >= 256) return run_conv_halo<256, 128, 4, 2, 2>(a, s, label);
-      if (blocks(128, 64) >= 256 && a.W > 4) return run_conv_halo<128, 64, 4, 2, 4>(a, s, label);
-      if (blocks(64, 64) >= 256) return run_conv_halo<64, 64, 2, 2, 4>(a, s, label);
-      return run_conv_halo<32, 64, 1, 4, 4>(a, s, label);
+      if (a.N > 64 && blocks(256, 128) >= 256) return run_conv_halo<256, 128, 4, 2, 2, 1>(a, s, label);
+      if (blocks(128, 64) >= 256 && a.W > 4) return run_conv_halo<128, 64, 4, 2, 4, 3>(a, s, label);
+      if (blocks(64, 64) >= 256) return run_conv_halo<64, 64, 2, 2, 3, 3>(a, s, label);
+      return run_conv_halo<32, 64, 1, 4, 3, 3>(a, s, label);
     }
     // 64 -> 32 at 32 x 32, 4 replicas: 59 us (128 x 32: 67; fp32 MFMA 107)
-    if (blocks(256, 32) >= 256) return run_conv_halo<256, 32, 8, 1, 4>(a, s, label);
-    return run_conv_halo<64, 32, 4, 1, 4>(a, s, label);
+    if (blocks(256, 32) >= 256) return run_conv_halo<256, 32, 8, 1, 4, 1>(a, s, label);
+    return run_conv_halo<64, 32, 4, 1, 4, 3>(a, s, label);
   }
   if (a.N > 64) {
     if (blocks(128, 128) >= 256) return run_conv<128, 128, 4, 2, 4>(a, s, label);
