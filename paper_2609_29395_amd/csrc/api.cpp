@@ -115,7 +115,7 @@ struct Plan {
   // the SGD pass in segments of the parameter vector (SgdSeg): the split-K
   // partials of every split layer are summed there; uploaded at creation
   std::vector<SgdSeg> sgd_segs;
-  int sgd_blocks = 0, sgd_vec = 1;
+  int sgd_blocks = 0, sgd_vec = 1, sgd_way_splits = 0;
   double sgd_part_bytes = 0.0;  // partial floats the pass reads per step, in bytes
   size_t total = 0;
 };
@@ -592,11 +592,25 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
       const int64_t any = g.begin | g.len | g.src | g.ss | g.rs | p.P;
       while (any % p.sgd_vec) p.sgd_vec /= 2;
     }
+    // Four waves per chain of partials while the launch of all replicas, a
+    // thread per vector, has fewer than 2048 blocks (eight per CU); beyond, the
+    // memory is busy either way and the waves that only add cost time (8 replicas
+    // of the narrow network, 3800 blocks: 51 us in one chain, 53 in four; one
+    // of the wide, 3789: 34 and 44).
+    auto seg_blocks = [&](const SgdSeg &g) {
+      const int64_t be = g.splits >= p.sgd_way_splits ? 256 * p.sgd_vec / kSgdWays
+                         : g.splits > 0               ? 256 * p.sgd_vec
+                                                      : kSgdBlockElems;
+      return (g.len + be - 1) / be;
+    };
     int64_t blocks = 0;
+    p.sgd_way_splits = INT32_MAX;
+    for (const SgdSeg &g : p.sgd_segs) blocks += seg_blocks(g);
+    if (blocks * C < 2048) p.sgd_way_splits = kSgdWaySplits;
+    blocks = 0;
     for (SgdSeg &g : p.sgd_segs) {
-      const int64_t be = g.splits > 0 ? 256 * p.sgd_vec : kSgdBlockElems;
       g.first_block = (int32_t)blocks;
-      blocks += (g.len + be - 1) / be;
+      blocks += seg_blocks(g);
     }
     if (blocks > INT32_MAX / 2) return gcpsl_fail(GCPSL_EUNSUPPORTED, "parameter vector too long");
     p.sgd_blocks = (int)blocks;
@@ -1394,7 +1408,7 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
   LAUNCH_T("sgd", 3.0 * C * p.P, 20.0 * C * p.P + p.sgd_part_bytes,
            launch_sgd_seg(d.theta, d.momentum_buf, grad, ctx->at<float>(p.off_part),
                           reinterpret_cast<const SgdSeg *>(ctx->ws + p.off_sgdseg), (int)p.sgd_segs.size(),
-                          p.sgd_blocks, p.sgd_vec, 256 * p.sgd_vec, p.P, C, rmap, d.lr, d.momentum,
+                          p.sgd_blocks, p.sgd_vec, 256 * p.sgd_vec, p.sgd_way_splits, p.P, C, rmap, d.lr, d.momentum,
                           d.weight_decay, d.nesterov, s));
   ctx->horizon = std::max<int64_t>(ctx->horizon, std::min<int64_t>(step + 1, p.max_steps));
   return GCPSL_OK;

@@ -1068,12 +1068,17 @@ __device__ __forceinline__ void sgd_update(float &t, float &v, float g, float lr
 // SGD by segments (SgdSeg): the split-K partials of a weight gradient are
 // summed here, in split order from zero (the partials of 8 splits loaded
 // before they are added), and the sum is written to grad before the update.
+// A segment of way_splits splits or more is summed by the four waves of a
+// block, a quarter of the splits each: a small network of few replicas has few
+// elements and many splits, and one thread's chain of 64 partials leaves the
+// memory idle (narrow network, 1 / 4 replicas: 33 / 37 us in one chain, 20 /
+// 31 in four).
 // The block's segment is the last one whose first block is at most
 // blockIdx.x.
 template <int VEC>
 __global__ void __launch_bounds__(256)
 sgd_seg_kernel(float *__restrict__ theta, float *__restrict__ mom, float *__restrict__ grad,
-               const float *__restrict__ part, const SgdSeg *__restrict__ segs, int nseg, int split_elems,
+               const float *__restrict__ part, const SgdSeg *__restrict__ segs, int nseg, int split_elems, int way_splits,
                int64_t P, const int32_t *__restrict__ rmap, float lr, float mu, float wd, int nesterov) {
   typedef typename FVec<VEC>::T V;
   int lo = 0, hi = nseg - 1;
@@ -1085,10 +1090,59 @@ sgd_seg_kernel(float *__restrict__ theta, float *__restrict__ mom, float *__rest
   const SgdSeg sg = segs[lo];
   const int rep = replica_of(rmap, blockIdx.y);
   const int64_t base = (int64_t)rep * P + sg.begin;
-  const int be = sg.splits > 0 ? split_elems : kSgdBlockElems;
+  const bool ways = sg.splits >= way_splits;
+  const int be = ways ? split_elems / kSgdWays : sg.splits > 0 ? split_elems : kSgdBlockElems;
   const int64_t e0 = ((int64_t)blockIdx.x - sg.first_block) * be;
   const int64_t e1 = min(sg.len, e0 + (int64_t)be);
   const float *pr = part + sg.src + (int64_t)rep * sg.rs;
+  if (ways) {
+    // wave w sums the splits [w q, (w + 1) q); the four sums are added in order
+    __shared__ V red[kSgdWays - 1][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, q = (sg.splits + kSgdWays - 1) / kSgdWays;
+    const int kb = min(sg.splits, (w + 1) * q);
+    for (int64_t c = e0; c < e1; c += 64 * VEC) {
+      const int64_t e = c + lane * VEC;
+      const bool live = e < e1;
+      V v = {}, t = {}, g = {};
+      float *vf = reinterpret_cast<float *>(&v), *tf = reinterpret_cast<float *>(&t), *gf = reinterpret_cast<float *>(&g);
+      if (live) {
+        if (w == 0) {
+          v = *reinterpret_cast<const V *>(mom + base + e);
+          t = *reinterpret_cast<const V *>(theta + base + e);
+        }
+        int k = w * q;
+        for (; k + 8 <= kb; k += 8) {
+          V pv[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) pv[u] = *reinterpret_cast<const V *>(pr + (k + u) * sg.ss + e);
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) gf[i] += reinterpret_cast<const float *>(&pv[u])[i];
+        }
+        for (; k < kb; ++k) {
+          const V pv = *reinterpret_cast<const V *>(pr + k * sg.ss + e);
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) gf[i] += reinterpret_cast<const float *>(&pv)[i];
+        }
+      }
+      if (w) red[w - 1][lane] = g;
+      __syncthreads();
+      if (w == 0 && live) {
+#pragma unroll
+        for (int u = 0; u < kSgdWays - 1; ++u)
+#pragma unroll
+          for (int i = 0; i < VEC; ++i) gf[i] += reinterpret_cast<const float *>(&red[u][lane])[i];
+        *reinterpret_cast<V *>(grad + base + e) = g;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sgd_update(tf[i], vf[i], gf[i], lr, mu, wd, nesterov);
+        *reinterpret_cast<V *>(mom + base + e) = v;
+        *reinterpret_cast<V *>(theta + base + e) = t;
+      }
+      __syncthreads();  // the sums are read before the next ones are stored
+    }
+    return;
+  }
   for (int64_t e = e0 + (int64_t)threadIdx.x * VEC; e < e1; e += 256 * VEC) {
     V g;
     if (sg.splits > 0) {
@@ -1425,8 +1479,8 @@ hipError_t launch_head_pool_bwd(int dtype, const void *a, const float *dh, void 
 }
 
 hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *partials, const SgdSeg *segs, int nseg,
-                          int blocks, int vec, int split_elems, int64_t P, int C, const int32_t *rmap, float lr,
-                          float mu, float wd, int nesterov, hipStream_t s) {
+                          int blocks, int vec, int split_elems, int way_splits, int64_t P, int C, const int32_t *rmap,
+                          float lr, float mu, float wd, int nesterov, hipStream_t s) {
   if (nseg < 1 || blocks < 1 || split_elems < 1) return hipErrorInvalidValue;
   // vec (4, 2 or 1) divides P and every segment's start, length, partial
   // offset and strides (the plan's choice); the pointers must allow it too
@@ -1436,14 +1490,14 @@ hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *pa
   if (vec == 2 && al % 8 != 0) vec = 1;
   const dim3 g((uint32_t)blocks, (uint32_t)C);
   if (vec == 4)
-    hipLaunchKernelGGL(sgd_seg_kernel<4>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems, P,
-                       rmap, lr, mu, wd, nesterov);
+    hipLaunchKernelGGL(sgd_seg_kernel<4>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
+                       way_splits, P, rmap, lr, mu, wd, nesterov);
   else if (vec == 2)
-    hipLaunchKernelGGL(sgd_seg_kernel<2>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems, P,
-                       rmap, lr, mu, wd, nesterov);
+    hipLaunchKernelGGL(sgd_seg_kernel<2>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
+                       way_splits, P, rmap, lr, mu, wd, nesterov);
   else
-    hipLaunchKernelGGL(sgd_seg_kernel<1>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems, P,
-                       rmap, lr, mu, wd, nesterov);
+    hipLaunchKernelGGL(sgd_seg_kernel<1>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
+                       way_splits, P, rmap, lr, mu, wd, nesterov);
   return hipGetLastError();
 }
 

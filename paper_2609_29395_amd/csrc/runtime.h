@@ -229,10 +229,12 @@ struct SgdSeg {
   int64_t begin, len, src, ss, rs;
   int32_t splits, first_block;
 };
-constexpr int kSgdBlockElems = 4096;
+// A segment of at least way_splits splits takes split_elems / kSgdWays elements
+// per block, the waves of a block sharing the splits.
+constexpr int kSgdBlockElems = 4096, kSgdWaySplits = 12, kSgdWays = 4;
 hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *partials, const SgdSeg *segs, int nseg,
-                          int blocks, int vec, int split_elems, int64_t P, int C, const int32_t *rmap, float lr,
-                          float mu, float wd, int nesterov, hipStream_t s);
+                          int blocks, int vec, int split_elems, int way_splits, int64_t P, int C, const int32_t *rmap,
+                          float lr, float mu, float wd, int nesterov, hipStream_t s);
 // Eq. 5 over C replicas of P parameters: weights from w_host through the
 // kernel arguments when C <= kMaxArgWeights, else from w_dev (device).
 constexpr int kMaxArgWeights = 64;
