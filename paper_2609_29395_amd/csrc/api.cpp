@@ -78,7 +78,8 @@ struct LayerInfo {
 // shortcut, ReLU: its output and gradient are the block's); with a
 // projection, cp (1 x 1, stride, on rows of the strided input) -> np (norm,
 // no ReLU) is the shortcut.  At stride 2 the input gradients of c1 and cp
-// take their output gradients spread back to the input grid (gup).
+// take their output gradients by classes of input pixels
+// (ConvArgs::stride2), or spread back to the input grid (gup).
 struct BlockInfo {
   int stride = 1;
   bool proj = false;
@@ -498,7 +499,7 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
         norm_buffers(bk.np);
         bk.gsc_off = take((size_t)p.esz * C * px_in * l.Ci);
       }
-      if (bk.stride == 2) bk.gup_off = take((size_t)p.esz * C * px_in * l.Co);
+      if (bk.stride == 2 && !conv_stride2(p.dtype, l.Co)) bk.gup_off = take((size_t)p.esz * C * px_in * l.Co);
       continue;
     }
     if (is_norm(kind)) {
@@ -1073,30 +1074,32 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
     return GCPSL_OK;
   };
   // input gradient of an internal conv over the input grid Hh x Ww: out =
-  // (sum + res) * [mask > 0] (res, mask optional); taps 9 (3 x 3 stride 1)
-  // or 1 (1 x 1)
+  // (sum + res) * [mask > 0] (res, mask optional); taps 9 (3 x 3) or 1 (1 x 1);
+  // stride2: src on the half grid (ConvArgs::stride2), else on the input's
   auto conv_dgrad = [&](const LayerInfo &cv, const void *src, int taps, int Hh, int Ww, void *out, const void *res,
-                        const void *mask) -> int {
+                        const void *mask, bool stride2 = false) -> int {
     ConvArgs a{};
     a.src = src;
     a.wt = ws + cv.wd_off;
     a.out = out;
     a.res = res;
     a.mask = mask;
-    a.Bt = B; a.H = Hh; a.W = Ww; a.Csrc = cv.Co; a.N = cv.Ci; a.K = taps * cv.Co; a.Kp = cv.Kdp;
-    a.src_rs = (int64_t)B * Hh * Ww * cv.Co;
+    const int sc = stride2 ? 2 : 1;
+    a.Bt = B; a.H = Hh / sc; a.W = Ww / sc; a.Csrc = cv.Co; a.N = cv.Ci; a.K = taps * cv.Co; a.Kp = cv.Kdp;
+    a.src_rs = (int64_t)B * a.H * a.W * cv.Co;
     a.wt_rs = (int64_t)cv.Ci * cv.Kdp;
     a.out_rs = (int64_t)B * Hh * Ww * cv.Ci;
     a.C = C;
     a.rmap = rmap;
     a.epi = EPI_DGRAD;
     a.taps = taps;
+    a.stride2 = stride2;
     std::string lab;
     const double M = (double)B * Hh * Ww;
     size_t t_ = tbegin(ctx, s);
     LAUNCH(launch_conv(p.dtype, a, s, &lab));
-    tend(ctx, s, t_, lab, 2.0 * C * M * cv.Ci * taps * cv.Co,
-         (double)C * p.esz * (M * cv.Co + (double)cv.Ci * taps * cv.Co + M * cv.Ci * (1 + (res ? 1 : 0) + (mask ? 1 : 0))));
+    tend(ctx, s, t_, lab, 2.0 * C * M / (sc * sc) * cv.Ci * taps * cv.Co,
+         (double)C * p.esz * (M / (sc * sc) * cv.Co + (double)cv.Ci * taps * cv.Co + M * cv.Ci * (1 + (res ? 1 : 0) + (mask ? 1 : 0))));
     return GCPSL_OK;
   };
   // weight and bias gradient of a conv from g (Hh x Ww pixels) and its input
@@ -1284,26 +1287,33 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
         return rc;
       LAUNCH_T(nn, 0.0, nby, launch_norm_bwd(p.dtype, nargs(bk.n1, ws + bk.c1.act_off, nullptr, ws + bk.n1.gpre_off,
                                                              ws + bk.c1.gpre_off, nullptr, 1), s));
+      // bf16 channel counts that break a 64-channel block: the output gradients of
+      // the strided convs are spread to the input grid (gup)
+      const bool spread = bk.stride == 2 && !conv_stride2(p.dtype, l.Co);
       const void *sc_grad = ws + l.gpre_off;  // identity shortcut: the gradient at the sum
       if (bk.proj) {
         LAUNCH_T(nn, 0.0, nby, launch_norm_bwd(p.dtype, nargs(bk.np, ws + bk.cp.act_off, nullptr, ws + l.gpre_off,
                                                                ws + bk.cp.gpre_off, nullptr, 0), s));
         if (int rc = wgrad_run(bk.cp, ws + bk.cp.gpre_off, ws + bk.xs_off, 1, bk.Kcp, l.Ho, l.Wo)) return rc;
         const void *g = ws + bk.cp.gpre_off;
-        if (bk.stride == 2) {
+        if (spread) {
           LAUNCH_T("zero_insert", 0.0, (double)C * p.esz * B * l.Co * (l.Ho * l.Wo + (double)l.H * l.W),
                    launch_zero_insert(p.dtype, g, ws + bk.gup_off, C, rmap, B, l.H, l.W, l.Ho, l.Wo, l.Co, s));
           g = ws + bk.gup_off;
         }
-        if (int rc = conv_dgrad(bk.cp, g, 1, l.H, l.W, ws + bk.gsc_off, nullptr, nullptr)) return rc;
+        if (int rc = conv_dgrad(bk.cp, g, 1, l.H, l.W, ws + bk.gsc_off, nullptr, nullptr, bk.stride == 2 && !spread))
+          return rc;
         sc_grad = ws + bk.gsc_off;
       }
       if (bk.stride == 2) {
         if (int rc = wgrad_run(bk.c1, ws + bk.c1.gpre_off, ws + bk.cols1_off, 1, bk.Kc1, l.Ho, l.Wo)) return rc;
-        LAUNCH_T("zero_insert", 0.0, (double)C * p.esz * B * l.Co * (l.Ho * l.Wo + (double)l.H * l.W),
-                 launch_zero_insert(p.dtype, ws + bk.c1.gpre_off, ws + bk.gup_off, C, rmap, B, l.H, l.W, l.Ho, l.Wo,
-                                    l.Co, s));
-        if (int rc = conv_dgrad(bk.c1, ws + bk.gup_off, 9, l.H, l.W, ws + prev.gpre_off, sc_grad, ws + prev.act_off))
+        const void *g = ws + bk.c1.gpre_off;
+        if (spread) {
+          LAUNCH_T("zero_insert", 0.0, (double)C * p.esz * B * l.Co * (l.Ho * l.Wo + (double)l.H * l.W),
+                   launch_zero_insert(p.dtype, g, ws + bk.gup_off, C, rmap, B, l.H, l.W, l.Ho, l.Wo, l.Co, s));
+          g = ws + bk.gup_off;
+        }
+        if (int rc = conv_dgrad(bk.c1, g, 9, l.H, l.W, ws + prev.gpre_off, sc_grad, ws + prev.act_off, !spread))
           return rc;
       } else {
         if (int rc = wgrad_run(bk.c1, ws + bk.c1.gpre_off, x, 9, l.Ci, l.H, l.W)) return rc;

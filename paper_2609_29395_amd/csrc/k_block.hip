@@ -7,8 +7,9 @@
 //                [wo*stride + s - pad][c], zero outside the image and in the
 //                padding columns up to Kc.  The forward and the weight
 //                gradient then take these rows as a one-tap product.
-//   zero_insert  a stride-2 conv's output gradient spread back to the input
-//                grid: gup[b][h][w] = g[b][h/2][w/2] at even (h, w), zero
+//   zero_insert  (bf16, output channels that are no multiple of 64: the others
+//                take the gradient by classes of input pixels) a stride-2
+//                conv's output gradient spread back to the input grid: gup[b][h][w] = g[b][h/2][w/2] at even (h, w), zero
 //                elsewhere.  The input gradient of a 3x3 / pad 1 (or 1x1 /
 //                pad 0) conv with stride 2 is then the stride-1 input
 //                gradient of gup (the inserted zeros add exact zeros), on
@@ -85,16 +86,12 @@ hipError_t launch_im2col(int dtype, const void *x, void *cols, int C, const int3
 
 hipError_t launch_zero_insert(int dtype, const void *g, void *gup, int C, const int32_t *rmap, int Bt, int H, int W,
                               int Ho, int Wo, int Ch, hipStream_t s) {
-  const int vec = dtype == GCPSL_BF16 ? 8 : 4;
-  if (Ch % vec) return hipErrorInvalidValue;
+  const int vec = ElemT<bf16_t>::VEC;
+  if (dtype != GCPSL_BF16 || Ch % vec) return hipErrorInvalidValue;
   const uint32_t total = (uint32_t)((int64_t)Bt * H * W * (Ch / vec));
   const dim3 grid((total + 255) / 256, C);
   const int64_t g_rs = (int64_t)Bt * Ho * Wo * Ch, u_rs = (int64_t)Bt * H * W * Ch;
-  if (dtype == GCPSL_BF16)
-    hipLaunchKernelGGL(zero_insert_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)g, (bf16_t *)gup, rmap,
-                       g_rs, u_rs, total, H, W, Ho, Wo, Ch);
-  else
-    hipLaunchKernelGGL(zero_insert_kernel<float>, grid, dim3(256), 0, s, (const float *)g, (float *)gup, rmap, g_rs,
-                       u_rs, total, H, W, Ho, Wo, Ch);
+  hipLaunchKernelGGL(zero_insert_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t *)g, (bf16_t *)gup, rmap, g_rs,
+                     u_rs, total, H, W, Ho, Wo, Ch);
   return hipGetLastError();
 }

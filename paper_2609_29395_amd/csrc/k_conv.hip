@@ -646,7 +646,13 @@ void wgrad_tile(int dtype, int Co, int ncols, int *bm, int *bn) {
   *bn = nw > 64 ? 128 : (nw > 32 ? 64 : 32);
 }
 
+bool conv_stride2(int dtype, int Csrc) { return Csrc % (dtype == GCPSL_BF16 ? 64 : 8) == 0; }
+
 hipError_t launch_conv(int dtype, const ConvArgs &a, hipStream_t s, std::string *label) {
+  if (a.stride2) {
+    if (a.epi != EPI_DGRAD || !conv_stride2(dtype, a.Csrc) || a.N % 8 != 0) return hipErrorInvalidValue;
+    return dtype == GCPSL_BF16 ? launch_conv_lds(a, s, label) : launch_conv_f32(a, s, label);
+  }
   // routing codes: the head's pooling epilogue (halo tile) and the
   // image-side kernels take them
   if (a.pool_code) {

@@ -159,13 +159,34 @@ __device__ float sum_conv(const ConvArgs &a, const float *src, const float *wt, 
   return s;
 }
 
+// The same of a stride-2 input gradient: (b, h, w) the class's pixel on the
+// output gradient's grid.
+__device__ float sum_conv(const ConvArgs &a, const float *src, const float *wt, int b, int h, int w, int n,
+                          const S2Class &cls) {
+  float s = 0.f;
+  for (int u = 0; u < cls.n; ++u) {
+    const float *wr = wt + (int64_t)n * a.Kp + cls.wtap(u) * a.Csrc;
+    const int hh = h + cls.di(u), ww = w + cls.dj(u);
+    const bool in = hh < a.H && ww < a.W;
+    const float *x = src + ((int64_t)(b * a.H + hh) * a.W + ww) * a.Csrc;
+    for (int c = 0; c < a.Csrc; ++c) s = fmaf(in ? x[c] : 0.f, wr[c], s);
+  }
+  return s;
+}
+
 // The tile's outputs from its sums: bias, residual, ReLU (forward) or
 // residual and ReLU mask (input gradient).
-template <int BM, int BN, int WM, int WN, int EPI>
+template <int BM, int BN, int WM, int WN, int EPI, bool S2 = false>
 __device__ __forceinline__ void conv_store(const ConvArgs &a, const f32x4_t (&acc)[BN / WN / 16][BM / WM / 16],
                                            const float *src, const float *wt, int rep, int m0, int n0, bool huge,
-                                           const FastDiv &fd_w, const FastDiv &fd_h) {
+                                           const FastDiv &fd_w, const FastDiv &fd_h, const S2Class &cls = S2Class(0, 9)) {
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  // output pixel of the tile's pixel m (classes: on the doubled grid)
+  auto opix = [&](int m) -> int64_t {
+    if constexpr (!S2) return m;
+    const int q1 = (int)fdiv((uint32_t)m, fd_w);
+    return (int64_t)(2 * q1 + cls.y) * (2 * a.W) + 2 * (m - q1 * a.W) + cls.x;
+  };
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, lg = lane >> 4;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
@@ -179,8 +200,9 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, const f32x4_t (&ac
       const int m = m0 + wm0 + e / (BN / WN), n = n0 + wn0 + e % (BN / WN);
       if (m >= M || n >= a.N) continue;
       const uint32_t q = fdiv((uint32_t)m, fd_w), b = fdiv(q, fd_h);
-      float v = sum_conv(a, src, wt, (int)b, (int)(q - b * (uint32_t)a.H), (int)((uint32_t)m - q * (uint32_t)a.W), n);
-      const int64_t o = (int64_t)m * a.N + n;
+      const int h = (int)(q - b * (uint32_t)a.H), w = (int)((uint32_t)m - q * (uint32_t)a.W);
+      float v = S2 ? sum_conv(a, src, wt, (int)b, h, w, n, cls) : sum_conv(a, src, wt, (int)b, h, w, n);
+      const int64_t o = opix(m) * a.N + n;
       if (EPI == EPI_FWD) v += bias[n];
       if (res) v += res[o];
       if (EPI == EPI_FWD && !a.no_relu) v = fmaxf(v, 0.f);
@@ -202,7 +224,7 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, const f32x4_t (&ac
     for (int i = 0; i < TM; ++i) {
       const int m = m0 + wm0 + i * 16 + li;
       if (m >= M || !nok) continue;
-      const int64_t o = (int64_t)m * a.N + n;
+      const int64_t o = opix(m) * a.N + n;
       f32x4_t v = acc[j][i];
       f32x4_t rv = {0.f, 0.f, 0.f, 0.f};
       if (res) rv = *reinterpret_cast<const f32x4_t *>(res + o);
@@ -229,8 +251,10 @@ __device__ __forceinline__ void conv_store(const ConvArgs &a, const f32x4_t (&ac
 
 // BM pixels x BN output channels per workgroup, WM x WN waves.  The weights
 // are the MFMA's first operand, so a lane ends with four consecutive channels
-// of one pixel: 16-byte stores, residual and mask loads.
-template <int BM, int BN, int WM, int WN, int EPI, int OCC>
+// of one pixel: 16-byte stores, residual and mask loads.  S2: the input gradient
+// of a stride-2 conv by classes of input pixels (ConvArgs::stride2), the class
+// of most taps first.
+template <int BM, int BN, int WM, int WN, int EPI, int OCC, bool S2 = false>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(OCC)))
 conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int NT) {
   constexpr int NTH = 64 * WM * WN, TM = BM / WM / 16, TN = BN / WN / 16;
@@ -241,7 +265,9 @@ conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
   __shared__ int huge;
 
   const int tid = threadIdx.x;
-  const uint32_t t = xcd_swizzle(blockIdx.x, (uint32_t)(MT * NT * a.C));
+  const uint32_t ntiles = (uint32_t)(MT * NT * a.C);
+  const S2Class cls(S2 ? __builtin_amdgcn_readfirstlane((int)(blockIdx.x / ntiles)) : 0, a.taps);
+  const uint32_t t = xcd_swizzle(S2 ? blockIdx.x % ntiles : blockIdx.x, ntiles);
   const int nt = __builtin_amdgcn_readfirstlane((int)(t % (uint32_t)NT));
   const uint32_t rest = t / (uint32_t)NT;
   const int mt = __builtin_amdgcn_readfirstlane((int)(rest % (uint32_t)MT));
@@ -279,26 +305,33 @@ conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
     offb[j] = (n < a.N && row < BN) ? ((uint32_t)n * (uint32_t)a.Kp + (uint32_t)(chunk * 8)) * 4u : kOob;
   }
 
+  const int K = S2 ? cls.n * a.Csrc : a.K;
   float top = 0.f;
   uint4 ra[AV][2], rb[BV][2];
   auto load = [&](int kt) {
     const int k0 = kt * kStep + chunk * 8;
     // tap and channel of the thread's 8 values (channels come in multiples of
     // 8 with 9 taps; im2col rows: multiples of 4, checked per 4 values)
-    const int rs = a.taps == 1 ? 4 : (int)fdiv((uint32_t)k0, fd_c);
-    const int c = k0 - (a.taps == 1 ? 0 : rs * a.Csrc);
+    int rs = !S2 && a.taps == 1 ? 4 : (int)fdiv((uint32_t)k0, fd_c);
+    const int c = k0 - (!S2 && a.taps == 1 ? 0 : rs * a.Csrc);
+    int kw = k0;  // weight column
+    if constexpr (S2) {
+      kw = cls.wtap(rs) * a.Csrc + c;
+      rs = 4 + 3 * cls.di(rs) + cls.dj(rs);
+    }
     const int r = (rs * 11) >> 5;  // rs / 3 for rs < 9
     const uint32_t tap = (uint32_t)((((r - 1) * a.W + (rs - 3 * r - 1)) * a.Csrc + c) * 4);
-    const bool live0 = k0 < a.K, live1 = k0 + 4 < a.K;  // (past the last stage: nothing is read)
+    const bool live0 = k0 < K, live1 = k0 + 4 < K;  // (past the last stage: nothing is read)
 #pragma unroll
     for (int j = 0; j < AV; ++j) {
-      const bool in = ((tapmask[j] >> rs) & 1u) != 0u;
+      const bool in = ((tapmask[j] >> (rs & 31)) & 1u) != 0u;
       ra[j][0] = buffer_load16(rsa, in && live0 ? rowoff[j] + tap : kOob);
       ra[j][1] = buffer_load16(rsa, in && live1 ? rowoff[j] + tap + 16u : kOob);
     }
 #pragma unroll
     for (int j = 0; j < BV; ++j) {
-      const uint32_t o = k0 < a.Kp ? offb[j] + (uint32_t)(kt * kStep * 4) : kOob;
+      const uint32_t o = S2 ? (k0 < K ? offb[j] + (uint32_t)((kw - chunk * 8) * 4) : kOob)
+                            : k0 < a.Kp ? offb[j] + (uint32_t)(kt * kStep * 4) : kOob;
       rb[j][0] = buffer_load16(rsb, o);
       rb[j][1] = buffer_load16(rsb, o + 16u);
     }
@@ -331,7 +364,7 @@ conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
   Sums<TN, TM> sums;
   sums.clear();
 
-  const int nk = (a.K + kStep - 1) / kStep;
+  const int nk = (K + kStep - 1) / kStep;
   if (tid == 0) huge = 0;
   load(0);
   for (int kt = 0; kt < nk; ++kt) {
@@ -356,7 +389,7 @@ conv_f32_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
   if (top >= kHuge) huge = 1;
   sums.finish();
   __syncthreads();
-  conv_store<BM, BN, WM, WN, EPI>(a, sums.hh, src, wt, rep, m0, n0, huge != 0, fd_w, fd_h);
+  conv_store<BM, BN, WM, WN, EPI, S2>(a, sums.hh, src, wt, rep, m0, n0, huge != 0, fd_w, fd_h, cls);
 }
 
 // The same contraction for 3 x 3 convs whose input channels fill 32-channel
@@ -932,6 +965,18 @@ hipError_t run_conv(const ConvArgs &a, hipStream_t s, std::string *label) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WM, int WN, int OCC>
+hipError_t run_stride2(const ConvArgs &a, hipStream_t s, std::string *label) {
+  const int M = a.Bt * a.H * a.W;
+  const int MT = (M + BM - 1) / BM, NT = (a.N + BN - 1) / BN;
+  if (label)
+    *label = "conv_dgrad<f32," + std::to_string(BM) + "x" + std::to_string(BN) + ",w" + std::to_string(WM * WN) +
+             ",stride2,split>";
+  hipLaunchKernelGGL((conv_f32_kernel<BM, BN, WM, WN, EPI_DGRAD, OCC, true>), dim3((uint32_t)MT * NT * a.C * 4),
+                     dim3(64 * WM * WN), 0, s, a, make_fastdiv(a.W), make_fastdiv(a.H), make_fastdiv(a.Csrc), MT, NT);
+  return hipGetLastError();
+}
+
 template <int BM, int BN, int WM, int WN, int OCC, int RD>
 hipError_t run_conv_halo(const ConvArgs &a, hipStream_t s, std::string *label) {
   const int M = a.Bt * a.H * a.W;
@@ -970,6 +1015,13 @@ hipError_t launch_conv_f32(const ConvArgs &a, hipStream_t s, std::string *label)
   if (a.Csrc % 4 != 0 || (a.taps != 1 && a.Csrc % 8 != 0) || a.N % 4 != 0) return hipErrorInvalidValue;
   const int64_t M = (int64_t)a.Bt * a.H * a.W;
   auto blocks = [&](int bm, int bn) { return (M + bm - 1) / bm * ((a.N + bn - 1) / bn) * a.C; };
+  if (a.stride2) {
+    // (the grid holds four classes; tiles as below, by the class of most taps)
+    if (a.N > 64 && blocks(128, 128) >= 256) return run_stride2<128, 128, 4, 2, 4>(a, s, label);
+    if (a.N > 32) return blocks(128, 64) >= 256 ? run_stride2<128, 64, 2, 2, 3>(a, s, label)
+                                                : run_stride2<64, 64, 2, 2, 4>(a, s, label);
+    return run_stride2<32, 32, 2, 2, 4>(a, s, label);
+  }
   // Halo staging where 32-channel blocks waste less than a fifth of their
   // stages.  The largest tile that gives every CU a workgroup: a smaller one
   // reads and splits its operands more often per product, a larger one leaves

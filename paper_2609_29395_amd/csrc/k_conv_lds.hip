@@ -234,17 +234,15 @@ __device__ __forceinline__ void issue_tile(int kt, char *stage0, int wave, const
                                                boff[q] == kOob ? kOob : boff[q] + kb, 0, 0, 0);
 }
 
-// Unrolled loop: the copies of the tile at place U of a group (nine taps of a
-// channel block, three tiles of a one-tap product) whose first column is byte
-// c of a pixel's channels, into stage U % 3; aoff: this thread's pixel offsets
+// Unrolled loop: a tile's copies into stage U % 3, from byte ca of its pixels'
+// channels and byte cw of the weight rows; aoff: this thread's pixel offsets
 // for the tile's tap.
-template <typename CF, bool TAPS1, int U>
+template <typename CF, int U>
 __device__ __forceinline__ void issue_unrolled(char *stage0, const ConvArgs &a, const void *src, const void *wt,
-                                               const uint32_t *aoff, const uint32_t *boff, uint32_t c) {
+                                               const uint32_t *aoff, const uint32_t *boff, uint32_t ca, uint32_t cw) {
   const __amdgpu_buffer_rsrc_t rsa = rsrc(src, (uint32_t)(a.src_rs * 2));
   const __amdgpu_buffer_rsrc_t rsb = rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
   char *sa = stage0 + (U % 3) * CF::STAGE;
-  const uint32_t ca = TAPS1 ? c + U * ROW : c, cw = TAPS1 ? ca : c + (uint32_t)(U * a.Csrc * 2);
 #pragma unroll
   for (int q = 0; q < CF::SA; ++q)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, LDS_PTR(sa + q * CF::NTHR * 16), 16, aoff[q], ca, 0, 0);
@@ -252,6 +250,16 @@ __device__ __forceinline__ void issue_unrolled(char *stage0, const ConvArgs &a, 
   for (int q = 0; q < CF::SB; ++q)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsb, LDS_PTR(sa + CF::A_BYTES + q * CF::NTHR * 16), 16, boff[q], cw, 0,
                                              0);
+}
+
+// The unrolled loop's turns: its first two tiles' copies, then the steps of a
+// turn in order until every tile is done.
+template <typename S, typename CP, int... U>
+__device__ __forceinline__ void unroll_steps(S &step, std::integer_sequence<int, U...>, int &k0, uint32_t &gcol,
+                                             uint32_t gstep, int nkt, CP &copy) {
+  copy(std::integral_constant<int, 0>{}, 0u);
+  if (nkt > 1) copy(std::integral_constant<int, 1>{}, 0u);
+  for (; k0 < nkt; k0 += (int)sizeof...(U), gcol += gstep) (step(std::integral_constant<int, U>{}), ...);
 }
 
 // Halo mode: piece q of channel block cb's halo image into buffer cb % HB
@@ -302,8 +310,13 @@ __device__ __forceinline__ void issue_weights(int kt, char *smem, int wave, cons
 // grid of one or two workgroups per CU has two to four waves per SIMD, too few
 // to hide the general loop's 120 instructions and two-stage copy latency per
 // tile.
+//
+// S2 (unrolled loop): the input gradient of a stride-2 conv by classes of input
+// pixels (ConvArgs::stride2), nine tap products per four pixels instead of the
+// 36 of the gradient spread to the input grid.  The workgroups of the class of
+// most taps come first.
 template <int BM, int BN, int WM, int WN, int EPI, bool TAPS1, bool HALO = false, bool AVG = false, int HB = 2,
-          bool UNROLL = false>
+          bool UNROLL = false, bool S2 = false>
 __global__ void __launch_bounds__(64 * WM * WN, (HALO && HB == 1) ? 4 : 1)
 conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int NT) {
   // one halo buffer: the two-pass epilogue keeps the staging within the
@@ -327,7 +340,10 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t tile = xcd_swizzle(blockIdx.x, (uint32_t)(MT * NT * a.C));
+  static_assert(!S2 || (UNROLL && EPI == EPI_DGRAD && !TAPS1), "classes run on the unrolled loop");
+  const uint32_t ntiles = (uint32_t)(MT * NT * a.C);
+  const S2Class cls(S2 ? __builtin_amdgcn_readfirstlane((int)(blockIdx.x / ntiles)) : 0, a.taps);
+  const uint32_t tile = xcd_swizzle(S2 ? blockIdx.x % ntiles : blockIdx.x, ntiles);
   const int nt = __builtin_amdgcn_readfirstlane((int)(tile % (uint32_t)NT));
   const uint32_t rest = tile / (uint32_t)NT;
   const int mt = __builtin_amdgcn_readfirstlane((int)(rest % (uint32_t)MT));
@@ -432,64 +448,69 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
     issue(0);
   }
   if constexpr (UNROLL) {
-    constexpr int UN = TAPS1 ? 3 : 9, CPT = SA + SB;
-    uint32_t aoff[TAPS1 ? 1 : 9][SA];  // byte offset of this thread's copies, per tap
-#pragma unroll
-    for (int q = 0; q < SA; ++q)
-#pragma unroll
-      for (int t = 0; t < (TAPS1 ? 1 : 9); ++t) {
-        const int tap = TAPS1 ? 0 : ((t / 3 - 1) * a.W + (t % 3 - 1)) * a.Csrc;
-        aoff[t][q] = ((amask[q] >> t) & 1u) ? (uint32_t)(arowoff[q] + tap + 8 * achunk[q]) * 2u : kOob;
-      }
-    auto copy = [&](auto U, uint32_t c) {
-      constexpr int u = decltype(U)::value;
-      issue_unrolled<CF, TAPS1, u>(stage0, a, src, wt, aoff[TAPS1 ? 0 : u], boff, c);
-    };
+    constexpr int CPT = SA + SB;
     const uint32_t xr[2] = {lds0 + xa[0], lds0 + xa[1]}, wr[2] = {lds0 + wa[0], lds0 + wa[1]};
-    int k0 = 0;          // first tile of the group
-    uint32_t gcol = 0u;  // and its first column (bytes)
-    constexpr uint32_t GCOL = TAPS1 ? 3 * ROW : ROW;
-    auto step = [&](auto U) {
-      constexpr int u = decltype(U)::value;
-      if (TAPS1 && k0 + u >= nk) return;
-      // tile k0 + u has landed for every wave (copies land in issue order: the
-      // next tile's may stay in flight), and every wave is done with the tile
-      // before it, whose stage takes tile k0 + u + 2
-      if ((!TAPS1 && u < 8) || k0 + u + 1 < nk)
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPT) : "memory");
-      else
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      asm volatile("s_barrier" ::: "memory");
-      if ((!TAPS1 && u < 7) || k0 + u + 2 < nk)
-        copy(std::integral_constant<int, (u + 2) % UN>{}, gcol + (uint32_t)((u + 2) / UN) * GCOL);
-      u32x4 w0[TN], x0[TM], w1[TN], x1[TM];
-      constexpr int SO = (u % 3) * CF::STAGE;
-      read_at<SO>(w0, wr[0]);
-      read_at<SO>(x0, xr[0]);
-      read_at<SO>(w1, wr[1]);
-      read_at<SO>(x1, xr[1]);
-      wait_older<TM + TN>(x0, w0);
+    // nkt tiles of T taps per channel block
+    auto loop = [&](auto Tc, int nkt) {
+      constexpr int T = decltype(Tc)::value, UN = T == 9 ? 9 : 3 * T;  // tiles per turn: whole rounds of the stages
+      uint32_t aoff[T][SA], wcol[T];  // byte offset of this thread's copies and of the weights' columns, per tap
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
+      for (int t = 0; t < T; ++t) {
+        // source pixel's row and column from the tile's own, and its bit in amask
+        const int dr = S2 ? cls.di(t) : T == 9 ? t / 3 - 1 : 0, dc = S2 ? cls.dj(t) : T == 9 ? t % 3 - 1 : 0;
+        const int bit = TAPS1 ? 0 : (dr + 1) * 3 + dc + 1;
+        wcol[t] = (uint32_t)((S2 ? cls.wtap(t) : t) * a.Csrc * 2);
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w0[tn], x0[tm]);
-      __builtin_amdgcn_sched_barrier(0);
-      wait_older<0>(x1, w1);
+        for (int q = 0; q < SA; ++q)
+          aoff[t][q] = ((amask[q] >> bit) & 1u)
+                           ? (uint32_t)(arowoff[q] + (dr * a.W + dc) * a.Csrc + 8 * achunk[q]) * 2u : kOob;
+      }
+      int k0 = 0;          // first tile of the turn
+      uint32_t gcol = 0u;  // and its channel block's first column (bytes)
+      constexpr uint32_t GCOL = UN / T * ROW;
+      auto copy = [&](auto U, uint32_t c) {
+        constexpr int u = decltype(U)::value;
+        issue_unrolled<CF, u>(stage0, a, src, wt, aoff[u % T], boff, c + u / T * ROW, wcol[u % T] + c + u / T * ROW);
+      };
+      auto step = [&](auto U) {
+        constexpr int u = decltype(U)::value;
+        if (T < 9 && k0 + u >= nkt) return;
+        // tile k0 + u has landed for every wave (copies land in issue order: the
+        // next tile's may stay in flight), and every wave is done with the tile
+        // before it, whose stage takes tile k0 + u + 2
+        if ((T == 9 && u < 8) || k0 + u + 1 < nkt)
+          asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CPT) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
+        if ((T == 9 && u < 7) || k0 + u + 2 < nkt)
+          copy(std::integral_constant<int, (u + 2) % UN>{}, gcol + (uint32_t)((u + 2) / UN) * GCOL);
+        u32x4 w0[TN], x0[TM], w1[TN], x1[TM];
+        constexpr int SO = (u % 3) * CF::STAGE;
+        read_at<SO>(w0, wr[0]);
+        read_at<SO>(x0, xr[0]);
+        read_at<SO>(w1, wr[1]);
+        read_at<SO>(x1, xr[1]);
+        wait_older<TM + TN>(x0, w0);
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
+        for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w1[tn], x1[tm]);
+          for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w0[tn], x0[tm]);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_older<0>(x1, w1);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int tn = 0; tn < TN; ++tn) mma(acc[tm][tn], w1[tn], x1[tm]);
+      };
+      unroll_steps(step, std::make_integer_sequence<int, UN>{}, k0, gcol, GCOL, nkt, copy);
     };
-    auto steps = [&](auto... U) { (step(U), ...); };
-    copy(std::integral_constant<int, 0>{}, 0u);
-    if (nk > 1) copy(std::integral_constant<int, 1>{}, 0u);
-    for (; k0 < nk; k0 += UN, gcol += GCOL) {
-      if constexpr (TAPS1)
-        steps(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
-      else
-        steps(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{},
-              std::integral_constant<int, 3>{}, std::integral_constant<int, 4>{}, std::integral_constant<int, 5>{},
-              std::integral_constant<int, 6>{}, std::integral_constant<int, 7>{}, std::integral_constant<int, 8>{});
+    if constexpr (S2) {
+      if (cls.n == 4) loop(std::integral_constant<int, 4>{}, 4 * ncb);
+      else if (cls.n == 2) loop(std::integral_constant<int, 2>{}, 2 * ncb);
+      else if (cls.n == 1) loop(std::integral_constant<int, 1>{}, ncb);
+    } else {
+      loop(std::integral_constant<int, TAPS1 ? 1 : 9>{}, nk);
     }
   }
   if constexpr (!UNROLL)
@@ -621,6 +642,12 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
   bf16_t *out = reinterpret_cast<bf16_t *>(a.out) + rep * a.out_rs;
   const bf16_t *res = (a.res && !a.res_lds) ? reinterpret_cast<const bf16_t *>(a.res) + rep * a.out_rs : nullptr;
   const bf16_t *msk = a.mask ? reinterpret_cast<const bf16_t *>(a.mask) + rep * a.out_rs : nullptr;
+  // output pixel of the tile's pixel m (classes: on the doubled grid)
+  auto opix = [&](int m) -> int64_t {
+    if constexpr (!S2) return m;
+    const int q1 = (int)fdiv((uint32_t)m, fd_w);
+    return (int64_t)(2 * q1 + cls.y) * (2 * a.W) + 2 * (m - q1 * a.W) + cls.x;
+  };
   const __amdgpu_buffer_rsrc_t rsr = rsrc(res ? res : out, (uint32_t)(a.out_rs * 2));
   const __amdgpu_buffer_rsrc_t rsm = rsrc(msk ? msk : out, (uint32_t)(a.out_rs * 2));
   // dgrad: the mask loads of every pass are issued up front, so their HBM
@@ -636,7 +663,7 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
 #pragma unroll
       for (int i = 0; i < ITS; ++i) {
         const int m = m0 + wm * TM * 16 + pass * PR + lane / SEGS + RSTEP * i;
-        const uint32_t off = (nok && m < M) ? (uint32_t)((int64_t)m * a.N + n) * 2u : kOob;
+        const uint32_t off = (nok && m < M) ? (uint32_t)(opix(m) * a.N + n) * 2u : kOob;
         mvall[pass][i] = msk ? __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsm, off, 0, 0))
                              : make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);
       }
@@ -658,7 +685,7 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
 #pragma unroll
     for (int i = 0; i < ITS; ++i) {
       const int m = m0 + wm * TM * 16 + pass * PR + lane / SEGS + RSTEP * i;
-      const uint32_t off = (nok && m < M) ? (uint32_t)((int64_t)m * a.N + n) * 2u : kOob;
+      const uint32_t off = (nok && m < M) ? (uint32_t)(opix(m) * a.N + n) * 2u : kOob;
       rv[i] = res ? __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsr, off, 0, 0))
                   : make_uint4(0, 0, 0, 0);
     }
@@ -696,7 +723,7 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
       ov.z = pack2_bf16(v[4], v[5]);
       ov.w = pack2_bf16(v[6], v[7]);
       // (with the pool's routing codes the output itself is not kept)
-      if (nok && m < M && !(AVG && a.pool_code)) *reinterpret_cast<uint4 *>(out + (int64_t)m * a.N + n) = ov;
+      if (nok && m < M && !(AVG && a.pool_code)) *reinterpret_cast<uint4 *>(out + opix(m) * a.N + n) = ov;
       if constexpr (AVG) {
         // the stored (bf16-rounded) values, as the pooling reads them back
         const uint32_t ow[4] = {ov.x, ov.y, ov.z, ov.w};
@@ -898,7 +925,8 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
     for (const void *f : {reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_FWD, false, false, false, 2, true>),
                           reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_FWD, true, false, false, 2, true>),
                           reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, false, false, false, 2, true>),
-                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, true, false, false, 2, true>)}) {
+                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, true, false, false, 2, true>),
+                          reinterpret_cast<const void *>(&conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, false, false, false, 2, true, true>)}) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, UnrollCfg::LDS_BYTES);
       if (e != hipSuccess) return e;
     }
@@ -908,6 +936,15 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
     CONV_LDS_ATTR(256, 64, 4, 2)
     CONV_LDS_ATTR(256, 32, 4, 2)
     attr.mark();
+  }
+  if (a.stride2) {
+    int MT, NT;
+    grid<128, 64>(a, &MT, &NT);
+    if (label) *label = "conv_dgrad<bf16,128x64x64,w8,stride2>";
+    hipLaunchKernelGGL((conv_lds_kernel<128, 64, 4, 2, EPI_DGRAD, false, false, false, 2, true, true>),
+                       dim3((uint32_t)MT * NT * a.C * 4), dim3(UnrollCfg::NTHR), (UnrollCfg::LDS_BYTES), s, a,
+                       make_fastdiv(a.W), make_fastdiv(a.H), make_fastdiv(a.Csrc), MT, NT);
+    return hipGetLastError();
   }
   // the narrowest weight tile that covers N (256 beyond 128); a 64-wide
   // tile over a long k loop takes 128 pixels (48 KB of LDS: three

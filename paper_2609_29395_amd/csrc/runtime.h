@@ -73,6 +73,30 @@ struct ConvArgs {
   int64_t code_rs;  // fwd with the head's mean of a max pool in pool_out (kernels that report
                     // conv_fuses_avg): the pool's routing codes [C][Bt][H/2][W/2][N] go to
                     // pool_code, this its per-replica stride, and `out` is not written
+  // dgrad of a stride-2 conv (kernels that report conv_stride2): H, W, src are
+  // the output gradient's grid, out, res and mask the input's, 2 H x 2 W.  The
+  // input pixels (2 i + y, 2 j + x) of a class (y, x) take the taps that reach
+  // them: tap rows 1 (y = 0) or 0 and 2 (y = 1) of the copy in wt, from output
+  // rows i, or i and i + 1, and the same for columns; a 1 x 1 conv (taps 1)
+  // reaches class (0, 0) only, the others get zero (+ res).
+  int stride2;
+};
+
+// Class c of a stride-2 input gradient (0 the one of most taps): rows and
+// columns y, x, taps, and tap u's source pixel (row u / nx, column u % nx past
+// the class's own) and weight tap.
+struct S2Class {
+  int y, x, nx, n, one;  // one: 1 x 1
+  __host__ __device__ S2Class(int c, int taps) {
+    y = c == 0 || c == 1;
+    x = c == 0 || c == 2;
+    nx = 1 + x;
+    one = taps == 1;
+    n = one ? (c == 3) : (1 + y) * nx;
+  }
+  __host__ __device__ int di(int u) const { return u / nx; }
+  __host__ __device__ int dj(int u) const { return u % nx; }
+  __host__ __device__ int wtap(int u) const { return one ? 0 : (y ? 2 * di(u) : 1) * 3 + (x ? 2 * dj(u) : 1); }
 };
 
 // Weight gradient: dW[co][kk] = sum_p G[p][co] X(p, kk), kk = (r, s, ci),
@@ -139,6 +163,9 @@ bool wgrad_pool_codes(int dtype, int Co, int Ci, int H, int W, int taps);
 // 256-wide halo tile, every output channel in one tile).
 bool conv_fuses_avg(int dtype, const ConvArgs &a);
 hipError_t launch_conv_img(const ConvArgs &a, hipStream_t s, std::string *label);
+// Whether launch_conv takes ConvArgs::stride2 for Csrc channels: fp32, or whole
+// 64-channel blocks in bf16 (others spread the gradient to the input grid).
+bool conv_stride2(int dtype, int Csrc);
 // bf16 forward / dgrad with LDS-direct tile copies (k_conv_lds.hip).
 bool conv_lds_ok(int dtype, const ConvArgs &a);
 hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label);

@@ -58,11 +58,11 @@ def kernel_label(name: str) -> str:
         t = "bf16" if m.group(1) == "unsigned short" else "f32"
         w = int(m.group(4)) * int(m.group(5))
         return f"conv_wgrad<{t},{m.group(2)}x{m.group(3)},w{w},{'vec' if m.group(6) == 'true' else 'gather'}>"
-    m = re.search(r"conv_f32_(halo_)?kernel<(\d+), (\d+), (\d+), (\d+), (\d)", name)
+    m = re.search(r"conv_f32_(halo_)?kernel<(\d+), (\d+), (\d+), (\d+), (\d)(, \d)?(, true)?", name)
     if m:  # fp32 on the bf16 matrix cores
         kind = "conv_fwd" if m.group(6) == "0" else "conv_dgrad"
         return (f"{kind}<f32,{m.group(2)}x{m.group(3)},w{int(m.group(4)) * int(m.group(5))},"
-                f"{'halo,' if m.group(1) else ''}split>")
+                f"{'halo,' if m.group(1) else ''}{'stride2,' if m.group(8) else ''}split>")
     if re.search(r"wgrad_f32_halo_kernel\b", name):
         return "conv_wgrad<f32,64x288,w4,halo,split>"
     m = re.search(r"wgrad_f32_kernel<(\d+), (\d+), (\d+), (\d+)", name)
@@ -70,11 +70,12 @@ def kernel_label(name: str) -> str:
         return f"conv_wgrad<f32,{m.group(1)}x{m.group(2)},w{int(m.group(3)) * int(m.group(4))},split>"
     # (an optional last flag marks the halo forward that also writes the image means)
     m = re.search(r"conv_lds_kernel<(\d+), (\d+), (\d+), (\d+), (\d), (true|false)(, (true|false))?"
-                  r"(, (true|false))?(, (\d))?(, (true|false))?>", name)
+                  r"(, (true|false))?(, (\d))?(, (true|false))?(, (true|false))?>", name)
     if m:
         kind = "conv_fwd" if m.group(5) == "0" else "conv_dgrad"
         w = int(m.group(3)) * int(m.group(4))
-        mode = "halo" if m.group(8) == "true" else "unroll" if m.group(14) == "true" else "lds"
+        mode = ("halo" if m.group(8) == "true" else "stride2" if m.group(16) == "true"
+                else "unroll" if m.group(14) == "true" else "lds")
         if mode == "halo" and m.group(12) == "1":  # one halo buffer
             return f"{kind}<bf16,{m.group(1)}x{m.group(2)}x64,w{w},halo1>"
         kt = 192 if (mode == "halo" and m.group(2) == "64") else 64  # tap-row k tiles
@@ -120,7 +121,7 @@ def kernel_source(label: str) -> str:
         return "k_conv_f32.hip"
     if label.startswith("conv_wgrad<") and label.endswith((",lds>", ",halo>", ",img>", ",col>", ",img3>", ",pool>")):
         return "k_wgrad_lds.hip"
-    if label.startswith("conv_") and label.endswith((",lds>", ",unroll>", ",halo>", ",halo1>")):
+    if label.startswith("conv_") and label.endswith((",lds>", ",unroll>", ",stride2>", ",halo>", ",halo1>")):
         return "k_conv_lds.hip"
     if label.startswith("conv_") and label.endswith((",img>", ",col>", ",img3>", ",img,pool>")):
         return "k_conv_img.hip"

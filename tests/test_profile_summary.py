@@ -37,6 +37,10 @@ def test_other_labels():
                            "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_fwd<bf16,128x64x64,w8,lds>"
     assert ps.kernel_label("void (anonymous namespace)::conv_lds_kernel<128, 64, 4, 2, 1, true, false, false, 2, true>"
                            "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_dgrad<bf16,128x64x64,w8,unroll>"
+    assert ps.kernel_label("void (anonymous namespace)::conv_lds_kernel<128, 64, 4, 2, 1, false, false, false, 2, true, true>"
+                           "(ConvArgs, FastDiv, FastDiv, FastDiv, int, int)") == "conv_dgrad<bf16,128x64x64,w8,stride2>"
+    assert ps.kernel_label("void (anonymous namespace)::conv_f32_kernel<128, 64, 2, 2, 1, 3, true>(ConvArgs)") == \
+        "conv_dgrad<f32,128x64,w4,stride2,split>"
 
 
 def test_image_layer_labels():
