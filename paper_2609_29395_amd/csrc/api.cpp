@@ -116,6 +116,10 @@ struct Plan {
   // the SGD pass in segments of the parameter vector (SgdSeg): the split-K
   // partials of every split layer are summed there; uploaded at creation
   std::vector<SgdSeg> sgd_segs;
+  // the head in parts of head_per examples: their sums start head_src floats
+  // from off_part, strides head_ss (parts) and head_rs (replicas)
+  int head_per = 0, head_parts = 1;
+  int64_t head_src = 0, head_ss = 0, head_rs = 0;
   int sgd_blocks = 0, sgd_vec = 1, sgd_way_splits = 0;
   double sgd_part_bytes = 0.0;  // partial floats the pass reads per step, in bytes
   size_t total = 0;
@@ -573,6 +577,33 @@ int build_plan(const gcpsl_desc *d, Plan &p) {
     // SGD segments: each split layer's weights and biases from its partials,
     // the rest of the parameter vector from grad; kSgdBlockElems per block
     std::vector<SgdSeg> segs;
+    // The head in parts of at least 8 examples (one per wave), eight of them at
+    // most.  A part's sums go where a conv's forward weights lie, read for the
+    // last time before the head and written again by the next round.
+    {
+      const LayerInfo &li = p.ly[p.lin_idx];
+      const int64_t floats = ((int64_t)li.nw + li.Co + 1 + 3) / 4 * 4;
+      const LayerInfo *at = nullptr;
+      int64_t room = 0;  // floats of a replica's copy
+      auto look = [&](const LayerInfo &cv) {
+        const int64_t f = (int64_t)cv.Co * cv.Kp * p.esz / 4;
+        if (cv.nw && f > room) at = &cv, room = f;
+      };
+      for (const LayerInfo &l : p.ly) {
+        if (l.spec.kind == GCPSL_CONV3X3) look(l);
+        if (l.spec.kind == GCPSL_BLOCK) look(p.blocks[l.blk].c1), look(p.blocks[l.blk].c2);
+      }
+      const int parts = (int)std::min<int64_t>(std::min(8, (B + 7) / 8), room / floats);
+      p.head_per = parts > 1 ? (B + parts - 1) / parts : B;
+      p.head_parts = (B + p.head_per - 1) / p.head_per;
+      if (p.head_parts > 1) {
+        p.head_src = ((int64_t)at->wf_off - (int64_t)p.off_part) / 4;
+        p.head_ss = floats;
+        p.head_rs = room;
+        segs.push_back(SgdSeg{li.w_off, li.nw + li.Co, p.head_src, p.head_ss, p.head_rs, p.head_parts, 0});
+        p.sgd_part_bytes += 4.0 * C * p.head_parts * (li.nw + li.Co);
+      }
+    }
     for (const LayerInfo *l : split_layers) {
       segs.push_back(SgdSeg{l->w_off, l->nw, (int64_t)l->part_off, (int64_t)C * l->nw, l->nw, l->splits, 0});
       segs.push_back(SgdSeg{l->b_off, l->Co, (int64_t)l->dbpart_off, (int64_t)C * l->Co, l->Co, l->splits, 0});
@@ -1252,7 +1283,9 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
       LAUNCH_T("linear_ce", 6.0 * C * B * l.Ci * l.Co,
                (double)C * (p.esz * B * l.Ci + 4.0 * (2.0 * l.nw + B * l.Ci + B)),
                launch_linear_ce(p.dtype, ws + p.ly[p.avg_idx].act_off, y, d.theta, p.P, l.w_off, l.b_off, grad,
-                                ctx->at<float>(p.off_dh), loss, C, rmap, B, l.Ci, l.Co, d.label_smoothing, s));
+                                ctx->at<float>(p.off_dh), loss, C, rmap, B, l.Ci, l.Co, d.label_smoothing,
+                                HeadParts{p.head_per, p.head_parts > 1 ? ctx->at<float>(p.off_part) + p.head_src : nullptr,
+                                          p.head_ss, p.head_rs}, s));
     }
   }
 
@@ -1419,7 +1452,10 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
            launch_sgd_seg(d.theta, d.momentum_buf, grad, ctx->at<float>(p.off_part),
                           reinterpret_cast<const SgdSeg *>(ctx->ws + p.off_sgdseg), (int)p.sgd_segs.size(),
                           p.sgd_blocks, p.sgd_vec, 256 * p.sgd_vec, p.sgd_way_splits, p.P, C, rmap, d.lr, d.momentum,
-                          d.weight_decay, d.nesterov, s));
+                          d.weight_decay, d.nesterov,
+                          HeadLoss{p.head_parts > 1 ? ctx->at<float>(p.off_part) + p.head_src + p.ly[p.lin_idx].nw +
+                                                          p.ly[p.lin_idx].Co : nullptr,
+                                   loss, p.head_ss, p.head_rs, p.head_parts, B}, s));
   ctx->horizon = std::max<int64_t>(ctx->horizon, std::min<int64_t>(step + 1, p.max_steps));
   return GCPSL_OK;
 }

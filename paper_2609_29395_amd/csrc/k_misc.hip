@@ -1,5 +1,6 @@
 // Sampling, gather, pools, the classifier head, SGD and fusion kernels.
 #include <algorithm>
+#include <type_traits>
 
 #include "rng.h"
 #include "runtime.h"
@@ -601,18 +602,19 @@ __global__ void __launch_bounds__(1024)
 linear_ce_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
                  const float *__restrict__ theta, int64_t P, int64_t w_off, int64_t b_off,
                  float *__restrict__ grad, float *__restrict__ dh, float *__restrict__ loss,
-                 const int32_t *__restrict__ rmap, int Bt, int Ch, int L, float eps) {
+                 const int32_t *__restrict__ rmap, int Ball, int Ch, int L, float eps, HeadParts hp) {
   extern __shared__ float sh[];
   // rows padded to Ch + 1 floats: threads of a wave that read the same
   // column of different rows hit different banks
   const int CP = Ch + 1;
+  const int lo = (int)blockIdx.y * hp.per, Bt = min(Ball - lo, hp.per);  // this workgroup's examples
   float *hs = sh;                      // [Bt][CP]
   float *ws = hs + (int64_t)Bt * CP;   // [L][CP]
   float *lg = ws + (int64_t)L * CP;    // [Bt][L] logits, then dlogits
   float *lossb = lg + Bt * L;          // [Bt]
   float *bs = lossb + Bt;              // [L] bias
   const int rep = replica_of(rmap, blockIdx.x), tid = threadIdx.x, nt = blockDim.x;
-  const T *hr = h + (int64_t)rep * Bt * Ch;
+  const T *hr = h + ((int64_t)rep * Ball + lo) * Ch;
   const float *Wl = theta + rep * P + w_off;
   const float *bl = theta + rep * P + b_off;
   // staging: whole 16-byte vectors when rows hold them, several loads in
@@ -635,20 +637,18 @@ linear_ce_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
   for (int i = tid; i < L * Ch; i += nt) ws[(i / Ch) * CP + i % Ch] = ElemT<T>::to_f(ElemT<T>::from_f(Wl[i]));
   for (int j = tid; j < L; j += nt) bs[j] = bl[j];
   __syncthreads();
-  for (int i = tid; i < Bt * L; i += nt) {
+  // eight lanes per logit, each with every eighth channel (whole groups of
+  // lanes take the same turns)
+  for (int i = tid >> 3; i < Bt * L; i += nt >> 3) {
     const int b = i / L, j = i % L;
     const float *hb = hs + (int64_t)b * CP, *wj = ws + (int64_t)j * CP;
-    // two partial sums over unrolled runs keep several LDS reads in flight
-    float s0 = 0.f, s1 = 0.f;
-    int c = 0;
-#pragma unroll 4
-    for (; c + 1 < Ch; c += 2) {
-      s0 += hb[c] * wj[c];
-      s1 += hb[c + 1] * wj[c + 1];
-    }
-    if (c < Ch) s0 += hb[c] * wj[c];
-    float s = bs[j] + (s0 + s1);
-    lg[i] = s;
+    float s0 = 0.f;
+#pragma unroll 8
+    for (int c = tid & 7; c < Ch; c += 8) s0 += hb[c] * wj[c];
+    s0 += __shfl_xor(s0, 1, 64);
+    s0 += __shfl_xor(s0, 2, 64);
+    s0 += __shfl_xor(s0, 4, 64);
+    if ((tid & 7) == 0) lg[i] = bs[j] + s0;
   }
   __syncthreads();
   for (int b = tid; b < Bt; b += nt) {
@@ -657,7 +657,7 @@ linear_ce_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
     float s = 0.f;
     for (int j = 0; j < L; ++j) s += expf(lg[b * L + j] - m);
     const float lse = logf(s);
-    const int yb = y[(int64_t)rep * Bt + b];
+    const int yb = y[(int64_t)rep * Ball + lo + b];
     // target q = (1 - eps) onehot(y) + eps / L; loss -sum_j q_j log p_j
     const float qo = eps / (float)L, qy = 1.f - eps + qo;
     float zs = 0.f;
@@ -665,16 +665,16 @@ linear_ce_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
     lossb[b] = eps > 0.f ? lse - (1.f - eps) * (lg[b * L + yb] - m) - qo * zs : lse - (lg[b * L + yb] - m);
     for (int j = 0; j < L; ++j) {
       const float p = expf(lg[b * L + j] - m - lse);
-      lg[b * L + j] = (p - (j == yb ? qy : qo)) / (float)Bt;
+      lg[b * L + j] = (p - (j == yb ? qy : qo)) / (float)Ball;
     }
   }
   __syncthreads();
   if (tid == 0) {
     float s = 0.f;
     for (int b = 0; b < Bt; ++b) s += lossb[b];
-    loss[rep] = s / (float)Bt;
+    *hp.loss(loss, rep, L, Ch) = hp.sums ? s : s / (float)Ball;
   }
-  float *g = grad + rep * P;
+  float *gw = hp.weights(grad + rep * P + w_off, rep), *gb = hp.biases(grad + rep * P + b_off, rep, L, Ch);
   for (int i = tid; i < L * Ch; i += nt) {
     const int j = i / Ch, c = i % Ch;
     float s0 = 0.f, s1 = 0.f;
@@ -685,14 +685,14 @@ linear_ce_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
       s1 += lg[(b + 1) * L + j] * hs[(int64_t)(b + 1) * CP + c];
     }
     if (b < Bt) s0 += lg[b * L + j] * hs[(int64_t)b * CP + c];
-    g[w_off + i] = s0 + s1;
+    gw[i] = s0 + s1;
   }
   for (int j = tid; j < L; j += nt) {
     float s = 0.f;
     for (int b = 0; b < Bt; ++b) s += lg[b * L + j];
-    g[b_off + j] = s;
+    gb[j] = s;
   }
-  float *dhr = dh + (int64_t)rep * Bt * Ch;
+  float *dhr = dh + ((int64_t)rep * Ball + lo) * Ch;
   for (int i = tid; i < Bt * Ch; i += nt) {
     const int b = i / Ch, c = i % Ch;
     float s = 0.f;
@@ -775,15 +775,16 @@ __device__ __forceinline__ void wave_sum16(float (&v)[NB][kHeadRegL], float (&su
   for (int u = 0; u < NB; ++u) sum[u] += t[u];
 }
 
-template <typename T, int LM>
+template <typename T, int LM, int NB>
 __global__ void __launch_bounds__(kHeadRegWaves * 64)
 linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
                      const float *__restrict__ theta, int64_t P, int64_t w_off, int64_t b_off,
                      float *__restrict__ grad, float *__restrict__ dh, float *__restrict__ loss,
-                     const int32_t *__restrict__ rmap, int Bt, int Ch, int L, float eps) {
+                     const int32_t *__restrict__ rmap, int Ball, int Ch, int L, float eps, HeadParts hp) {
   static_assert(LM % 4 == 0 && LM <= kHeadRegL, "class slots");
-  constexpr int NW = kHeadRegWaves, NB = 4;  // NB examples' loads in flight per wave
+  constexpr int NW = kHeadRegWaves;  // NB examples of a wave at a time, their loads in flight together
   extern __shared__ float sh[];
+  const int lo = (int)blockIdx.y * hp.per, Bt = min(Ball - lo, hp.per);  // this workgroup's examples
   float *lg = sh;               // [Bt][L] logits, then dlogits
   float *lossb = lg + Bt * L;   // [Bt]
   float4 *red = reinterpret_cast<float4 *>(sh + ((Bt * (L + 1) + 3) & ~3));  // [NW / 2][L][64]
@@ -792,7 +793,7 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
   const int c0 = 4 * lane;
   const bool live = c0 < Ch;
   const int cl = live ? c0 : 0;  // a valid channel for every lane
-  const T *hr = h + (int64_t)rep * Bt * Ch + cl;
+  const T *hr = h + ((int64_t)rep * Ball + lo) * Ch + cl;
   const float *Wl = theta + rep * P + w_off;
   const float *bl = theta + rep * P + b_off;
   float w[LM][4];
@@ -803,7 +804,7 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
       const float v = Wl[(int64_t)min(j, L - 1) * Ch + cl + e];
       w[j][e] = (live && j < L) ? ElemT<T>::to_f(ElemT<T>::from_f(v)) : 0.f;
     }
-  const int y0 = tid < Bt ? y[(int64_t)rep * Bt + tid] : 0;
+  const int y0 = tid < Bt ? y[(int64_t)rep * Ball + lo + tid] : 0;
   const int jl = (lane >> 2) & (kHeadRegL - 1);  // the logit this lane's sum ends as
   const bool writer = (lane & 3) == 0 && jl < L;
   const float bias = bl[min(jl, L - 1)];
@@ -844,14 +845,14 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
     float s = 0.f;
     for (int j = 0; j < L; ++j) s += expf(lg[b * L + j] - m);
     const float lse = logf(s);
-    const int yb = b == tid ? y0 : y[(int64_t)rep * Bt + b];
+    const int yb = b == tid ? y0 : y[(int64_t)rep * Ball + lo + b];
     const float qo = eps / (float)L, qy = 1.f - eps + qo;
     float zs = 0.f;
     for (int j = 0; j < L; ++j) zs += lg[b * L + j] - m;
     lossb[b] = eps > 0.f ? lse - (1.f - eps) * (lg[b * L + yb] - m) - qo * zs : lse - (lg[b * L + yb] - m);
     for (int j = 0; j < L; ++j) {
       const float p = expf(lg[b * L + j] - m - lse);
-      lg[b * L + j] = (p - (j == yb ? qy : qo)) / (float)Bt;
+      lg[b * L + j] = (p - (j == yb ? qy : qo)) / (float)Ball;
     }
   }
   __syncthreads();
@@ -859,7 +860,7 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
   // interleaved partial sums added in a fixed order (8 LDS reads in flight
   // instead of one), by the last wave, which has no more head work than
   // the others
-  float *g = grad + rep * P;
+  float *gw = hp.weights(grad + rep * P + w_off, rep), *gb = hp.biases(grad + rep * P + b_off, rep, L, Ch);
   if (wave == NW - 1 && lane <= L) {
     const float *col = lane < L ? lg + lane : lossb;  // lane L: the losses
     const int st = lane < L ? L : 1;
@@ -874,8 +875,8 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
     for (int k = 0; k < 8; ++k)
       if (b + k < Bt) p8[k] += col[(b + k) * st];
     const float sm = ((p8[0] + p8[1]) + (p8[2] + p8[3])) + ((p8[4] + p8[5]) + (p8[6] + p8[7]));
-    if (lane < L) g[b_off + lane] = sm;
-    else loss[rep] = sm / (float)Bt;
+    if (lane < L) gb[lane] = sm;
+    else *hp.loss(loss, rep, L, Ch) = hp.sums ? sm : sm / (float)Ball;
   }
 
   // input gradient of each example, weight-gradient share of each wave
@@ -884,7 +885,7 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
   for (int j = 0; j < LM; ++j)
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[j][e] = 0.f;
-  float *dhr = dh + (int64_t)rep * Bt * Ch + cl;
+  float *dhr = dh + ((int64_t)rep * Ball + lo) * Ch + cl;
 #pragma unroll
   for (int u = 0; u < NB; ++u) head_load4(hr + (int64_t)min(wave + u * NW, Bt - 1) * Ch, xn[u]);
   for (int b0 = wave; b0 < Bt; b0 += NB * NW) {
@@ -950,30 +951,39 @@ linear_ce_reg_kernel(const T *__restrict__ h, const int32_t *__restrict__ y,
     for (int j = 0; j < LM; ++j)
       if (j < L)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) g[w_off + (int64_t)j * Ch + c0 + e] = acc[j][e];
+        for (int e = 0; e < 4; ++e) gw[(int64_t)j * Ch + c0 + e] = acc[j][e];
   }
 }
 
 template <typename T>
 static hipError_t launch_linear_ce_reg(const T *h, const int32_t *y, const float *theta, int64_t P, int64_t w_off,
                                        int64_t b_off, float *grad, float *dh, float *loss, int C,
-                                       const int32_t *rmap, int Bt, int Ch, int L, float eps, hipStream_t s) {
-  const size_t shm = linear_ce_reg_lds_bytes(Bt, L);
+                                       const int32_t *rmap, int Bt, int Ch, int L, float eps, const HeadParts &hp,
+                                       hipStream_t s) {
+  const size_t shm = linear_ce_reg_lds_bytes(hp.per, L);
   auto go = [&](auto kern) -> hipError_t {
     if (shm > 64 * 1024) {
       const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(C), dim3(kHeadRegWaves * 64), shm, s, h, y, theta, P, w_off, b_off, grad, dh,
-                       loss, rmap, Bt, Ch, L, eps);
+    hipLaunchKernelGGL(kern, dim3(C, (Bt + hp.per - 1) / hp.per), dim3(kHeadRegWaves * 64), shm, s, h, y, theta, P, w_off, b_off, grad, dh,
+                       loss, rmap, Bt, Ch, L, eps, hp);
     return hipGetLastError();
   };
+  // (a wave has one or two examples in most parts: larger groups would only
+  // repeat the last one)
+  auto groups = [&](auto lm) -> hipError_t {
+    constexpr int LM = decltype(lm)::value;
+    if (hp.per <= kHeadRegWaves) return go(linear_ce_reg_kernel<T, LM, 1>);
+    if (hp.per <= 2 * kHeadRegWaves) return go(linear_ce_reg_kernel<T, LM, 2>);
+    return go(linear_ce_reg_kernel<T, LM, 4>);
+  };
   switch ((L + 3) / 4) {
-    case 1: return go(linear_ce_reg_kernel<T, 4>);
-    case 2: return go(linear_ce_reg_kernel<T, 8>);
-    case 3: return go(linear_ce_reg_kernel<T, 12>);
-    default: return go(linear_ce_reg_kernel<T, 16>);
+    case 1: return groups(std::integral_constant<int, 4>{});
+    case 2: return groups(std::integral_constant<int, 8>{});
+    case 3: return groups(std::integral_constant<int, 12>{});
+    default: return groups(std::integral_constant<int, 16>{});
   }
 }
 
@@ -1079,7 +1089,8 @@ template <int VEC>
 __global__ void __launch_bounds__(256)
 sgd_seg_kernel(float *__restrict__ theta, float *__restrict__ mom, float *__restrict__ grad,
                const float *__restrict__ part, const SgdSeg *__restrict__ segs, int nseg, int split_elems, int way_splits,
-               int64_t P, const int32_t *__restrict__ rmap, float lr, float mu, float wd, int nesterov) {
+               int64_t P, const int32_t *__restrict__ rmap, float lr, float mu, float wd, int nesterov,
+               HeadLoss hl) {
   typedef typename FVec<VEC>::T V;
   int lo = 0, hi = nseg - 1;
   while (lo < hi) {
@@ -1089,6 +1100,11 @@ sgd_seg_kernel(float *__restrict__ theta, float *__restrict__ mom, float *__rest
   }
   const SgdSeg sg = segs[lo];
   const int rep = replica_of(rmap, blockIdx.y);
+  if (hl.sums && blockIdx.x == 0 && threadIdx.x == 0) {
+    float sum = 0.f;
+    for (int k = 0; k < hl.parts; ++k) sum += hl.sums[k * hl.ss + (int64_t)rep * hl.rs];
+    hl.loss[rep] = sum / (float)hl.Bt;
+  }
   const int64_t base = (int64_t)rep * P + sg.begin;
   const bool ways = sg.splits >= way_splits;
   const int be = ways ? split_elems / kSgdWays : sg.splits > 0 ? split_elems : kSgdBlockElems;
@@ -1445,13 +1461,15 @@ hipError_t launch_head_pool(int dtype, const void *a, void *h, int C, const int3
 
 hipError_t launch_linear_ce(int dtype, const void *h, const int32_t *y, const float *theta, int64_t P,
                             int64_t w_off, int64_t b_off, float *grad, float *dh, float *loss, int C,
-                            const int32_t *rmap, int Bt, int Ch, int L, float eps, hipStream_t s) {
+                            const int32_t *rmap, int Bt, int Ch, int L, float eps, const HeadParts &hp,
+                            hipStream_t s) {
+  if (hp.per < 1 || (hp.per < Bt && !hp.sums)) return hipErrorInvalidValue;
   if (linear_ce_reg_ok(Bt, Ch, L))
     return dtype == GCPSL_BF16 ? launch_linear_ce_reg((const bf16_t *)h, y, theta, P, w_off, b_off, grad, dh, loss,
-                                                      C, rmap, Bt, Ch, L, eps, s)
+                                                      C, rmap, Bt, Ch, L, eps, hp, s)
                                : launch_linear_ce_reg((const float *)h, y, theta, P, w_off, b_off, grad, dh, loss,
-                                                      C, rmap, Bt, Ch, L, eps, s);
-  const size_t shm = linear_ce_lds_bytes(Bt, Ch, L);
+                                                      C, rmap, Bt, Ch, L, eps, hp, s);
+  const size_t shm = linear_ce_lds_bytes(hp.per, Ch, L);
   if (shm > kMaxLinearLds) return hipErrorInvalidValue;
   if (shm > 64 * 1024) {
     const hipError_t e = dtype == GCPSL_BF16
@@ -1461,12 +1479,13 @@ hipError_t launch_linear_ce(int dtype, const void *h, const int32_t *y, const fl
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
     if (e != hipSuccess) return e;
   }
+  const int parts = (Bt + hp.per - 1) / hp.per;
   if (dtype == GCPSL_BF16)
-    hipLaunchKernelGGL(linear_ce_kernel<bf16_t>, dim3(C), dim3(1024), shm, s, (const bf16_t *)h, y,
-                       theta, P, w_off, b_off, grad, dh, loss, rmap, Bt, Ch, L, eps);
+    hipLaunchKernelGGL(linear_ce_kernel<bf16_t>, dim3(C, parts), dim3(1024), shm, s, (const bf16_t *)h, y,
+                       theta, P, w_off, b_off, grad, dh, loss, rmap, Bt, Ch, L, eps, hp);
   else
-    hipLaunchKernelGGL(linear_ce_kernel<float>, dim3(C), dim3(1024), shm, s, (const float *)h, y,
-                       theta, P, w_off, b_off, grad, dh, loss, rmap, Bt, Ch, L, eps);
+    hipLaunchKernelGGL(linear_ce_kernel<float>, dim3(C, parts), dim3(1024), shm, s, (const float *)h, y,
+                       theta, P, w_off, b_off, grad, dh, loss, rmap, Bt, Ch, L, eps, hp);
   return hipGetLastError();
 }
 
@@ -1480,7 +1499,7 @@ hipError_t launch_head_pool_bwd(int dtype, const void *a, const float *dh, void 
 
 hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *partials, const SgdSeg *segs, int nseg,
                           int blocks, int vec, int split_elems, int way_splits, int64_t P, int C, const int32_t *rmap,
-                          float lr, float mu, float wd, int nesterov, hipStream_t s) {
+                          float lr, float mu, float wd, int nesterov, const HeadLoss &hl, hipStream_t s) {
   if (nseg < 1 || blocks < 1 || split_elems < 1) return hipErrorInvalidValue;
   // vec (4, 2 or 1) divides P and every segment's start, length, partial
   // offset and strides (the plan's choice); the pointers must allow it too
@@ -1491,13 +1510,13 @@ hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *pa
   const dim3 g((uint32_t)blocks, (uint32_t)C);
   if (vec == 4)
     hipLaunchKernelGGL(sgd_seg_kernel<4>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
-                       way_splits, P, rmap, lr, mu, wd, nesterov);
+                       way_splits, P, rmap, lr, mu, wd, nesterov, hl);
   else if (vec == 2)
     hipLaunchKernelGGL(sgd_seg_kernel<2>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
-                       way_splits, P, rmap, lr, mu, wd, nesterov);
+                       way_splits, P, rmap, lr, mu, wd, nesterov, hl);
   else
     hipLaunchKernelGGL(sgd_seg_kernel<1>, g, dim3(256), 0, s, theta, mom, grad, partials, segs, nseg, split_elems,
-                       way_splits, P, rmap, lr, mu, wd, nesterov);
+                       way_splits, P, rmap, lr, mu, wd, nesterov, hl);
   return hipGetLastError();
 }
 

@@ -231,13 +231,38 @@ inline size_t linear_ce_reg_lds_bytes(int Bt, int L) {
 inline bool linear_ce_reg_ok(int Bt, int Ch, int L) {
   return Ch % 4 == 0 && Ch <= 256 && L <= kHeadRegL && linear_ce_reg_lds_bytes(Bt, L) <= kMaxLinearLds;
 }
+// The head's examples in parts of `per`, one workgroup each (one workgroup per
+// replica is bound by its instructions on one CU: 128 examples of 256 channels
+// 27 -> 12 us, 64 of 128 18 -> 10, 64 of 512 47 -> 12): with `sums` (more than one
+// part), part k of replica r leaves its sums of the weight gradient,
+// the bias gradient and the losses one after another at sums + k ss + r rs for
+// the SGD pass to add; else the one part writes the gradient and the mean loss.
+struct HeadParts {
+  int per;
+  float *sums;
+  int64_t ss, rs;
+  __device__ float *weights(float *grad, int r) const { return sums ? sums + blockIdx.y * ss + r * rs : grad; }
+  __device__ float *biases(float *grad, int r, int L, int Ch) const {
+    return sums ? weights(nullptr, r) + (int64_t)L * Ch : grad;
+  }
+  __device__ float *loss(float *out, int r, int L, int Ch) const {
+    return sums ? weights(nullptr, r) + (int64_t)L * Ch + L : out + r;
+  }
+};
+// The losses' sums of a head in parts: loss[r] = their sum / Bt.
+struct HeadLoss {
+  const float *sums;  // or null
+  float *loss;
+  int64_t ss, rs;
+  int parts, Bt;
+};
 // The classifier head (linear layer and softmax cross-entropy, one workgroup
-// per replica): the register-resident kernel where linear_ce_reg_ok holds,
+// per replica and part): the register-resident kernel where linear_ce_reg_ok holds,
 // else the LDS-staged one.
 hipError_t launch_linear_ce(int dtype, const void *h, const int32_t *y, const float *theta,
                             int64_t P, int64_t w_off, int64_t b_off, float *grad, float *dh,
                             float *loss, int C, const int32_t *rmap, int Bt, int Ch, int L, float eps,
-                            hipStream_t s);
+                            const HeadParts &hp, hipStream_t s);
 // maxpool with code (bf16, the head conv's routing codes [C][Bt][H/2][W/2][Ch],
 // per-replica stride code_rs): the gradient is routed through the codes and
 // `a` is not read
@@ -261,7 +286,7 @@ struct SgdSeg {
 constexpr int kSgdBlockElems = 4096, kSgdWaySplits = 12, kSgdWays = 4;
 hipError_t launch_sgd_seg(float *theta, float *mom, float *grad, const float *partials, const SgdSeg *segs, int nseg,
                           int blocks, int vec, int split_elems, int way_splits, int64_t P, int C, const int32_t *rmap,
-                          float lr, float mu, float wd, int nesterov, hipStream_t s);
+                          float lr, float mu, float wd, int nesterov, const HeadLoss &hl, hipStream_t s);
 // Eq. 5 over C replicas of P parameters: weights from w_host through the
 // kernel arguments when C <= kMaxArgWeights, else from w_dev (device).
 constexpr int kMaxArgWeights = 64;
