@@ -1046,6 +1046,7 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
     na.chunk_px = norm_chunk((int64_t)B * l.H * l.W, p.C);
     na.chunks = (int)(((int64_t)B * l.H * l.W + na.chunk_px - 1) / na.chunk_px);
     na.C = C;
+    na.Call = p.C;
     na.rmap = rmap;
     return na;
   };
@@ -1070,6 +1071,7 @@ int run_round(gcpsl_ctx *ctx, int64_t step, const int32_t *rmap, int nrep, float
     na.chunk_px = norm_chunk((int64_t)B * nl.H * nl.W, p.C);
     na.chunks = (int)(((int64_t)B * nl.H * nl.W + na.chunk_px - 1) / na.chunk_px);
     na.C = C;
+    na.Call = p.C;
     na.rmap = rmap;
     na.res = res;
     na.relu = relu;

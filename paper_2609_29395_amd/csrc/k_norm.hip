@@ -746,9 +746,10 @@ template <typename T, int SV, int MODE> void run_bn_sv(const NormArgs &a, hipStr
 }
 template <typename T, int MODE> void run_bn(const NormArgs &a, hipStream_t s) {
   // (the fp64 sums bound a workgroup: two vectors each only where that still
-  // gives 128 of them)
+  // gives 128 of them in a launch of all the context's replicas; a launch of
+  // fewer takes the same slices, whose pixel lanes set the order of the sums)
   const int CV = a.Ch / ElemT<T>::VEC;
-  if (CV % 2 == 0 && CV / 2 * a.C >= 128)
+  if (CV % 2 == 0 && CV / 2 * a.Call >= 128)
     run_bn_sv<T, 2, MODE>(a, s);
   else
     run_bn_sv<T, 1, MODE>(a, s);

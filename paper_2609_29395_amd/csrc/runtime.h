@@ -315,6 +315,8 @@ struct NormArgs {
   int Bt, H, W, Ch, groups, nstat;
   int chunks, chunk_px;  // pixel chunks of the channel reductions
   int C;                 // replica slots
+  int Call;              // the context's replicas: what decides how a sum is split, so that a replica's
+                         // results do not depend on who shares its launch
   const int32_t *rmap;   // device [C]: replica of each slot, or null
   const void *res = nullptr;  // forward: added to gamma x_hat + beta before the ReLU (a block's shortcut), or null
   int relu = 1;               // forward: 1 applies the ReLU, 0 stores gamma x_hat + beta (a shortcut's norm)

@@ -8,7 +8,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from gcpsl_inputs import get_config  # noqa: E402
-from paper_2609_29395_amd import driver  # noqa: E402
+from paper_2609_29395_amd import driver, gcpsl  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +47,43 @@ def test_norm_round_against_the_oracle(dtype, side, B, C, w1, g1, w2, g2, w3):
                      momentum=0.9, F=0, T=1, dtype=dtype)
     ctx, o, theta0, losses, _ = matched_run(cfg, 1)
     check_run(ctx, o, theta0, losses, cfg)
+
+
+# 256 pixels per cluster (one launch), 512 channels: four clusters take two
+# channel vectors per workgroup, one alone would take one.  Sums over the same
+# values in another order agree in fp64 to far below an fp32 spacing, so the
+# images make the order visible: each batch holds every image and its negative,
+# with magnitudes over 2^40, and two small images besides, so a channel's sum
+# cancels to the small images' while its partial sums round at 2^-53 of the large.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_serial_clusters_of_small_batch_norms_bit_for_bit(dtype):
+    side, B, C, ch = 4, 16, 4, 512
+    rng = np.random.default_rng(7)
+    images, clients = [], []
+    for n in range(C):
+        x = rng.standard_normal((7, side, side, 3)) * 2.0 ** rng.uniform(0, 40, (7, side, side, 3))
+        images += [x, -x, rng.standard_normal((2, side, side, 3))]
+        clients += [n] * B
+    w = rng.uniform(-0.2, 0.2, (ch, 27))
+    theta = np.concatenate([w.ravel(), np.zeros(ch), np.ones(ch), np.zeros(ch), rng.uniform(-0.05, 0.05, 4 * ch),
+                            np.zeros(4)]).astype(np.float32)
+    cfg = dict(K=C, C=C, B=B, L=4, H=side, W=side, Cin=3, N_ex=C * B, dtype=dtype, lr=0.01, momentum=0.9, seed=0,
+               layers=[("conv", 3, ch, False), ("bnorm", ch), ("avgpool",), ("linear", ch, 4)], cut=2)
+    state0 = np.concatenate([np.zeros(ch), np.ones(ch), np.zeros(1)]).astype(np.float32)
+    labels = rng.integers(0, 4, C * B).astype(np.int32)
+    out = []
+    for serial in (False, True):
+        ctx = gcpsl.Context(cfg, np.concatenate(images).astype(np.float32), labels, np.array(clients, np.int32),
+                            np.arange(C, dtype=np.int32), theta, max_steps=1, norm_state0=state0)
+        loss = torch.zeros(C, device="cuda")
+        ctx.sample(0)
+        if serial:
+            for n in range(C):
+                ctx.step_replica(0, n, loss)
+        else:
+            ctx.step(0, loss)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (loss, ctx.theta, ctx.mom, ctx.norm_state)])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
