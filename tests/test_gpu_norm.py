@@ -49,7 +49,7 @@ def test_norm_round_against_the_oracle(dtype, side, B, C, w1, g1, w2, g2, w3):
     check_run(ctx, o, theta0, losses, cfg)
 
 
-# 256 pixels per cluster (one launch), 512 channels: four clusters take two
+# 1,024 pixels per cluster (one launch), 512 channels: four clusters take two
 # channel vectors per workgroup, one alone would take one.  Sums over the same
 # values in another order agree in fp64 to far below an fp32 spacing, so the
 # images make the order visible: each batch holds every image and its negative,
@@ -57,11 +57,11 @@ def test_norm_round_against_the_oracle(dtype, side, B, C, w1, g1, w2, g2, w3):
 # cancels to the small images' while its partial sums round at 2^-53 of the large.
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_serial_clusters_of_small_batch_norms_bit_for_bit(dtype):
-    side, B, C, ch = 4, 16, 4, 512
+    side, B, C, ch = 4, 64, 4, 512
     rng = np.random.default_rng(7)
     images, clients = [], []
     for n in range(C):
-        x = rng.standard_normal((7, side, side, 3)) * 2.0 ** rng.uniform(0, 40, (7, side, side, 3))
+        x = rng.standard_normal((31, side, side, 3)) * 2.0 ** rng.uniform(0, 40, (31, side, side, 3))
         images += [x, -x, rng.standard_normal((2, side, side, 3))]
         clients += [n] * B
     w = rng.uniform(-0.2, 0.2, (ch, 27))
