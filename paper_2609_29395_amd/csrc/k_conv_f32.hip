@@ -8,18 +8,19 @@
 //   x = h + m + l,  h = bf16(x), m = bf16(x - h), l = x - h - m
 //
 // (8 + 8 + 8 significant bits; each difference is exact, rounding to nearest
-// leaves |m| <= 2^-9 |x| and |l| <= 2^-18 |x|), and a product x y is the six
+// leaves |m| <= 2^-8 |x| and |l| <= 2^-17 |x|), and a product x y is the six
 // terms l h' + h l' + m m' + m h' + h m' + h h' on v_mfma_f32_16x16x32_bf16,
-// accumulated in fp32.  The three terms left out are below 2^-26 |x y|, a
-// quarter of the fp32 rounding of one product.  (Below 2^-110 the last parts
-// run out of the bf16 exponent range: absolute precision 2^-133.)
+// accumulated in fp32.  The three terms left out, m l' + l m' + l l', reach
+// 2^-24 |x y| at worst, the fp32 rounding of one product (what the sums are off
+// as a whole: Sums below).  (Below 2^-110 the last parts run out of the bf16
+// exponent range: absolute precision 2^-133.)
 //
 // Sums that are not finite: a NaN gives NaN in all six terms, as in fp32.
 // But an infinity has no such split (inf - inf), a value within half a bf16
-// spacing of FLT_MAX rounds to one, and terms of opposite sign may overflow.
-// So the staging threads keep the largest magnitude they split; where it is
-// 2^60 or more (below that no sum overflows), a wave whose tile holds a sum
-// that is not finite takes it again in plain fp32 (sum_* below), and
+// spacing of FLT_MAX rounds to one, and terms of opposite sign may overflow
+// here and not in the order of k.  So the staging threads keep the largest
+// magnitude they split; where it is kHuge or more, a wave whose tile holds a
+// sum that is not finite takes it again in plain fp32 (sum_* below), and
 // infinities come out as fp32 arithmetic gives them.
 //
 // Tiles are staged per 32 k values: every thread loads fp32 values into
@@ -138,7 +139,10 @@ __device__ __forceinline__ bool finite(const float *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) * 0.f == 0.f;
 }
 
-constexpr float kHuge = 0x1p60f;
+// Below this no sum overflows: products stay below 2^100, and no sum has 2^27
+// terms (a layer's tensors are below 2 GiB, so a weight gradient has at most
+// 2^26 pixels of 8 channels; the others have 9 taps of fewer than 2^14 channels).
+constexpr float kHuge = 0x1p50f;
 constexpr int kHaloW = 32;  // widest image of the halo kernel
 constexpr int kStep = 32;  // k values per stage
 

@@ -128,3 +128,30 @@ def test_values_that_round_to_infinity_in_bf16():
     got = grad[o:o + th[2].size].reshape(40, 3, 3, 40).transpose(1, 2, 0, 3)
     assert np.isfinite(got).all() and np.abs(want).max() > 1e25
     assert np.linalg.norm((got - want) / 1e25) <= 1e-4 * np.linalg.norm(want / 1e25)
+
+
+def test_sums_of_large_terms_that_cancel():
+    """Operands just below 2^60: the second layer's positive terms (its first 32
+    input channels, 288 products near 2^120) pass 2^128 when a block of channels
+    is summed over the taps first, while in the order of k, a tap's channels
+    together, the sum stays below: finite, as in plain fp32.  Every term is a
+    power of two times 255, so the sums are exact in either order but for fp32's
+    rounding, 576 x 2^-24 of the terms' magnitude."""
+    side, top = 5, np.float32(255 * 2.0**52)
+    layers = [("conv", 3, 64, False), ("conv", 64, 64, False), ("avgpool",), ("linear", 64, 4)]
+
+    def change(th):
+        th[0][:] = 0
+        th[0][:, 1, 1, 0] = top  # every activation of the first layer: top
+        th[1][:] = 0
+        th[2][:] = top
+        th[2][..., 32:] *= np.float32(-0.5)
+        th[3][:] = 0
+
+    images = np.ones((3, side, side, 3), np.float32)
+    (a0, a1), _, _, _, th = _round(images, layers, side, change)
+    assert (a0 == top).all()
+    want = _conv(a0.astype(np.float64), th[2], th[3])
+    terms = 1.5 * 32 * 9 * float(top)**2
+    assert want.max() < float(np.finfo(np.float32).max) < terms
+    assert np.isfinite(a1).all() and np.abs(a1 - want).max() <= 576 * 2.0**-24 * terms
