@@ -24,7 +24,8 @@
 // Group norm is one launch each way (and chan_finish for dgamma, dbeta): a
 // workgroup takes whole examples, so it has every value of its statistics,
 // and keeps the example in registers between the sums and the result where it
-// fits.  Batch norm of up to kBnPixels pixels per replica is one launch each
+// fits; a few examples that don't take the result in a second launch over the
+// chip.  Batch norm of up to kBnPixels pixels per replica is one launch each
 // way too: a workgroup takes a few channels of every pixel and reads them
 // twice (from L2).  Larger batch norms reduce chunks of pixels, finish the
 // sums and apply them in three launches; their chunks shrink for small
@@ -248,7 +249,8 @@ template <typename T> __device__ __forceinline__ void opaque(V16<T> &v) {
   v = __builtin_bit_cast(V16<T>, q);
 }
 
-template <typename T, int NT, int NV, int MAXC>
+// APPLY false: the statistics only (norm_apply_* write the result).
+template <typename T, int NT, int NV, int MAXC, bool APPLY = true>
 __global__ void __launch_bounds__(NT)
 group_fwd_kernel(NormArgs a) {
   constexpr int VEC = ElemT<T>::VEC, N = NV > 0 ? NV : 1;
@@ -296,6 +298,7 @@ group_fwd_kernel(NormArgs a) {
     a.mean[si] = gm[g] = (float)m;
     a.rstd[si] = gr[g] = (float)(1.0 / sqrt(var + kEps));
   }
+  if (!APPLY) return;
   __syncthreads();
   if (pl >= PL) return;
   const float *gamma = a.theta + rep * a.P + a.g_off, *beta = a.theta + rep * a.P + a.b_off;
@@ -336,8 +339,9 @@ group_fwd_kernel(NormArgs a) {
 
 // Backward: dz, and the channel sums of du and du x_hat of each workgroup's
 // `per` consecutive examples in part[rep][workgroup][c][2] (chan_finish adds
-// the workgroups in order).
-template <typename T, int NT, int NV, int MAXC>
+// the workgroups in order).  APPLY false: S1 and S2 of each group in sums[rep]
+// instead of dz.
+template <typename T, int NT, int NV, int MAXC, bool APPLY = true>
 __global__ void __launch_bounds__(NT)
 group_bwd_kernel(NormArgs a, int per) {
   constexpr int VEC = ElemT<T>::VEC, N = NV > 0 ? NV : 1;
@@ -408,9 +412,15 @@ group_bwd_kernel(NormArgs a, int per) {
         S2 += ls.chs[1][c] * gamma[c];
       }
       const double n = (double)HW * CG;
-      g1[g] = (float)(S1 / n), g2[g] = (float)(S2 / n);
+      if (APPLY) {
+        g1[g] = (float)(S1 / n), g2[g] = (float)(S2 / n);
+      } else {
+        double *o = a.sums + ((int64_t)rep * a.nstat + b * G + g) * 2;
+        o[0] = S1, o[1] = S2;
+      }
     }
     __syncthreads();
+    if (!APPLY) continue;
     float k1[VEC], k2[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
@@ -582,18 +592,24 @@ batch_norm_kernel(NormArgs a) {
   }
 }
 
-// The elementwise passes of large batch norms: a workgroup takes kApplyUnroll consecutive runs of
-// 256 16-byte vectors (four loads in flight per thread), so a thread keeps
-// the same VEC channels (256 is a multiple of the vectors per pixel) and
-// walks neighbouring pixels.  The per-channel values it needs (gamma, beta,
-// the statistics) are loaded when its channels change, not per element.
+// The elementwise passes of large batch norms, and of group norms (GROUPS) of a
+// few large examples: a workgroup takes kApplyUnroll consecutive runs of 256
+// 16-byte vectors (four loads in flight per thread), so a thread keeps the same
+// VEC channels (where 256 is a multiple of the vectors per pixel) and walks
+// neighbouring pixels.  The values it needs (gamma, beta, the statistics) are
+// loaded when its channels or its example change, not per element.
 constexpr int kApplyUnroll = 4;
+
+// statistics index of channel c of example b
+template <bool GROUPS> __device__ __forceinline__ int stat_index(const NormArgs &a, int b, int c) {
+  return GROUPS ? b * a.groups + c / (a.Ch / a.groups) : c;
+}
 
 // a = ReLU(gamma (z - mean) rstd + beta (+ res)) (without the ReLU for a
 // shortcut's norm).
-template <typename T>
+template <typename T, bool GROUPS>
 __global__ void __launch_bounds__(256)
-norm_apply_fwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
+norm_apply_fwd_kernel(NormArgs a, uint32_t total, FastDiv fcv, FastDiv fhw) {
   constexpr int VEC = ElemT<T>::VEC;
   const int rep = replica_of(a.rmap, blockIdx.y);
   const int CV = a.Ch / VEC;
@@ -603,7 +619,7 @@ norm_apply_fwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
   const float *mean = a.mean + (int64_t)rep * a.nstat, *rstd = a.rstd + (int64_t)rep * a.nstat;
   const float *gamma = a.theta + rep * a.P + a.g_off, *beta = a.theta + rep * a.P + a.b_off;
   constexpr uint32_t stride = 256u;
-  int kc = -1;  // channel vector of the cached values
+  int kc = -1, kb = 0;  // channel vector and example of the cached values
   float km[VEC], kr[VEC], kg[VEC], kbt[VEC];
   {
     const uint32_t i0 = blockIdx.x * (256u * kApplyUnroll) + threadIdx.x;
@@ -620,13 +636,14 @@ norm_apply_fwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
     for (int u = 0; u < kApplyUnroll; ++u) {
       const uint32_t i = i0 + u * stride;
       if (i >= total) break;
-      const int cv = (int)(i - fdiv(i, fcv) * CV);
-      if (cv != kc) {
-        kc = cv;
+      const uint32_t p = fdiv(i, fcv);
+      const int cv = (int)(i - p * CV), b = GROUPS ? (int)fdiv(p, fhw) : 0;
+      if (cv != kc || b != kb) {
+        kc = cv, kb = b;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          const int c = cv * VEC + e;
-          km[e] = mean[c], kr[e] = rstd[c], kg[e] = gamma[c], kbt[e] = beta[c];
+          const int c = cv * VEC + e, si = stat_index<GROUPS>(a, b, c);
+          km[e] = mean[si], kr[e] = rstd[si], kg[e] = gamma[c], kbt[e] = beta[c];
         }
       }
       V16<T> o;
@@ -643,9 +660,9 @@ norm_apply_fwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
 
 // dz = rstd (du gamma - S1 / n - x_hat S2 / n); batch norm's S1, S2 are gamma
 // times the per-channel sums.
-template <typename T>
+template <typename T, bool GROUPS>
 __global__ void __launch_bounds__(256)
-norm_apply_bwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
+norm_apply_bwd_kernel(NormArgs a, uint32_t total, FastDiv fcv, FastDiv fhw) {
   constexpr int VEC = ElemT<T>::VEC;
   const int rep = replica_of(a.rmap, blockIdx.y);
   const int CV = a.Ch / VEC;
@@ -655,9 +672,9 @@ norm_apply_bwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
   const float *mean = a.mean + (int64_t)rep * a.nstat, *rstd = a.rstd + (int64_t)rep * a.nstat;
   const float *gamma = a.theta + rep * a.P + a.g_off;
   const double *sums = a.sums + (int64_t)rep * a.nstat * 2;
-  const double n = (double)a.Bt * a.H * a.W;
+  const double n = GROUPS ? (double)a.H * a.W * (a.Ch / a.groups) : (double)a.Bt * a.H * a.W;
   constexpr uint32_t stride = 256u;
-  int kc = -1;
+  int kc = -1, kb = 0;
   float km[VEC], kr[VEC], kg[VEC], k1[VEC], k2[VEC];
   {
     const uint32_t i0 = blockIdx.x * (256u * kApplyUnroll) + threadIdx.x;
@@ -674,21 +691,24 @@ norm_apply_bwd_kernel(NormArgs a, uint32_t total, FastDiv fcv) {
     for (int u = 0; u < kApplyUnroll; ++u) {
       const uint32_t i = i0 + u * stride;
       if (i >= total) break;
-      const int cv = (int)(i - fdiv(i, fcv) * CV);
-      if (cv != kc) {
-        kc = cv;
+      const uint32_t p = fdiv(i, fcv);
+      const int cv = (int)(i - p * CV), b = GROUPS ? (int)fdiv(p, fhw) : 0;
+      if (cv != kc || b != kb) {
+        kc = cv, kb = b;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          const int c = cv * VEC + e;
-          km[e] = mean[c], kr[e] = rstd[c], kg[e] = gamma[c];
-          k1[e] = (float)(sums[2 * c] / n), k2[e] = (float)(sums[2 * c + 1] / n);
+          const int c = cv * VEC + e, si = stat_index<GROUPS>(a, b, c);
+          km[e] = mean[si], kr[e] = rstd[si], kg[e] = gamma[c];
+          k1[e] = (float)(sums[2 * si] / n), k2[e] = (float)(sums[2 * si + 1] / n);
         }
       }
       V16<T> o;
 #pragma unroll
       for (int e = 0; e < VEC; ++e) {
         const float xh = (ElemT<T>::to_f(zv[u].v[e]) - km[e]) * kr[e];
-        o.v[e] = ElemT<T>::from_f(kr[e] * kg[e] * (ElemT<T>::to_f(gv[u].v[e]) - k1[e] - xh * k2[e]));
+        const float g = ElemT<T>::to_f(gv[u].v[e]);
+        o.v[e] = ElemT<T>::from_f(GROUPS ? kr[e] * (g * kg[e] - k1[e] - xh * k2[e])
+                                         : kr[e] * kg[e] * (g - k1[e] - xh * k2[e]));
       }
       store16(dz + (int64_t)i * VEC, o);
     }
@@ -708,20 +728,39 @@ uint32_t apply_blocks(uint32_t total) {
 // again / fp32, 38 held; backward 37 read again / 53 held in bf16, 53 / 64 in
 // fp32: the second reading comes from the last-level cache, and the registers
 // of the held one spill).
-#define GCPSL_HOLD(MOST, CALL)                                                    \
-  do {                                                                           \
-    const int hw_ = a.H * a.W;                                                   \
-    const int n256_ = a.Ch <= 256 ? (hw_ + 256 / CV - 1) / (256 / CV) : 1 << 20; \
-    const int n512_ = a.Ch <= 512 ? (hw_ + 512 / CV - 1) / (512 / CV) : 1 << 20; \
-    if (n256_ <= 4)                                                              \
-      CALL(256, 4, 256);                                                         \
-    else if (n512_ <= 8)                                                         \
-      CALL(512, 8, 512);                                                         \
-    else if (n512_ <= (MOST))                                                    \
-      CALL(512, (MOST), 512);                                                    \
-    else                                                                         \
-      CALL(512, 0, 2048);                                                        \
+// group_vectors: the vectors of an example that a thread of NT then holds.
+int group_vectors(const NormArgs &a, int CV, int NT) {
+  const int PL = NT / CV;
+  return a.Ch <= NT ? (a.H * a.W + PL - 1) / PL : 1 << 20;
+}
+#define GCPSL_HOLD(MOST, CALL)                 \
+  do {                                         \
+    if (group_vectors(a, CV, 256) <= 4)        \
+      CALL(256, 4, 256);                       \
+    else if (group_vectors(a, CV, 512) <= 8)   \
+      CALL(512, 8, 512);                       \
+    else if (group_vectors(a, CV, 512) <= MOST) \
+      CALL(512, MOST, 512);                    \
+    else                                       \
+      CALL(512, 0, 2048);                      \
   } while (0)
+
+// Whether a group norm takes its result in an elementwise pass of its own: the
+// workgroup that has an example's sums would read it again and write it alone,
+// so fewer examples than kGroupSplit (of all the context's replicas) leave the
+// chip idle.  Forward and backward, us, in one kernel / with the pass, bf16 (fp32):
+//   64 channels of 64 x 64,    2 examples 105 /  78 (101 /  63)
+//                             32 examples 114 /  94 (115 /  83)
+//                             96 examples 122 / 122 (200 / 172)
+//   192 channels of 32 x 32,  32 examples  94 /  91  (96 /  81)
+//                             64 examples  99 / 110 (101 / 106)
+constexpr int kGroupSplit = 64;
+bool group_split(const NormArgs &a, int CV, int most) {
+  return (int64_t)a.Bt * a.Call < kGroupSplit && group_vectors(a, CV, 256) > 4 && group_vectors(a, CV, 512) > most;
+}
+// vectors a thread holds at most, forward and backward (where the registers end)
+constexpr int kHoldFwd = 16;
+template <typename T> constexpr int kHoldBwd = ElemT<T>::VEC == 4 ? 16 : 8;
 
 // Pixels per replica up to which a batch norm runs in one launch: its time is
 // that of one workgroup (M pixels x 32 bytes, read twice and written once at
@@ -760,17 +799,21 @@ hipError_t norm_fwd_t(const NormArgs &a, hipStream_t s) {
   constexpr int VEC = ElemT<T>::VEC;
   const int CV = a.Ch / VEC;
   const uint32_t total = (uint32_t)((int64_t)a.Bt * a.H * a.W * CV);
-  if (a.groups) {
+  const FastDiv fcv = make_fastdiv((uint32_t)CV), fhw = make_fastdiv((uint32_t)(a.H * a.W));
+  const dim3 apply(apply_blocks(total), a.C);
+  if (a.groups && group_split(a, CV, kHoldFwd)) {
+    hipLaunchKernelGGL((group_fwd_kernel<T, 512, 0, 2048, false>), dim3(a.Bt, a.C), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((norm_apply_fwd_kernel<T, true>), apply, dim3(256), 0, s, a, total, fcv, fhw);
+  } else if (a.groups) {
 #define FWD(NT, NV, MC) hipLaunchKernelGGL((group_fwd_kernel<T, NT, NV, MC>), dim3(a.Bt, a.C), dim3(NT), 0, s, a)
-    GCPSL_HOLD(16, FWD);
+    GCPSL_HOLD(kHoldFwd, FWD);
 #undef FWD
   } else if (bn_one_launch<T>(a)) {
     run_bn<T, 0>(a, s);
   } else {
-    const FastDiv fcv = make_fastdiv((uint32_t)CV);
     hipLaunchKernelGGL((chan_reduce_kernel<T, 0>), dim3(a.chunks, a.C), dim3(256), 0, s, a);
     hipLaunchKernelGGL((chan_finish_kernel<0>), dim3((a.Ch + kFinishCh - 1) / kFinishCh, a.C), dim3(256), 0, s, a);
-    hipLaunchKernelGGL((norm_apply_fwd_kernel<T>), dim3(apply_blocks(total), a.C), dim3(256), 0, s, a, total, fcv);
+    hipLaunchKernelGGL((norm_apply_fwd_kernel<T, false>), apply, dim3(256), 0, s, a, total, fcv, fhw);
   }
   return hipGetLastError();
 }
@@ -780,24 +823,30 @@ hipError_t norm_bwd_t(const NormArgs &a, hipStream_t s) {
   constexpr int VEC = ElemT<T>::VEC;
   const int CV = a.Ch / VEC;
   const uint32_t total = (uint32_t)((int64_t)a.Bt * a.H * a.W * CV);
-  const dim3 fin((a.Ch + kFinishCh - 1) / kFinishCh, a.C);
+  const FastDiv fcv = make_fastdiv((uint32_t)CV), fhw = make_fastdiv((uint32_t)(a.H * a.W));
+  const dim3 fin((a.Ch + kFinishCh - 1) / kFinishCh, a.C), apply(apply_blocks(total), a.C);
   if (a.groups) {
     // examples per workgroup: its partial sums fill at most the chunks' rows
     NormArgs f = a;
     const int per = (a.Bt + a.chunks - 1) / a.chunks;
     f.chunks = (a.Bt + per - 1) / per;
+    const bool split = group_split(a, CV, kHoldBwd<T>);
+    if (split) {
+      hipLaunchKernelGGL((group_bwd_kernel<T, 512, 0, 2048, false>), dim3(f.chunks, a.C), dim3(512), 0, s, f, per);
+    } else {
 #define BWD(NT, NV, MC) \
   hipLaunchKernelGGL((group_bwd_kernel<T, NT, NV, MC>), dim3(f.chunks, a.C), dim3(NT), 0, s, f, per)
-    GCPSL_HOLD((VEC == 4 ? 16 : 8), BWD);
+      GCPSL_HOLD(kHoldBwd<T>, BWD);
 #undef BWD
+    }
     hipLaunchKernelGGL((chan_finish_kernel<1>), fin, dim3(256), 0, s, f);
+    if (split) hipLaunchKernelGGL((norm_apply_bwd_kernel<T, true>), apply, dim3(256), 0, s, a, total, fcv, fhw);
   } else if (bn_one_launch<T>(a)) {
     run_bn<T, 1>(a, s);
   } else {
-    const FastDiv fcv = make_fastdiv((uint32_t)CV);
     hipLaunchKernelGGL((chan_reduce_kernel<T, 1>), dim3(a.chunks, a.C), dim3(256), 0, s, a);
     hipLaunchKernelGGL((chan_finish_kernel<1>), fin, dim3(256), 0, s, a);
-    hipLaunchKernelGGL((norm_apply_bwd_kernel<T>), dim3(apply_blocks(total), a.C), dim3(256), 0, s, a, total, fcv);
+    hipLaunchKernelGGL((norm_apply_bwd_kernel<T, false>), apply, dim3(256), 0, s, a, total, fcv, fhw);
   }
   return hipGetLastError();
 }
