@@ -26,12 +26,15 @@
 // works on 8 consecutive channels per lane: 16-byte loads of the residual and
 // mask (all of a pass issued together), 16-byte stores.
 //
-// Residual layers add the layer input itself (cin == cout).  With 64-channel
-// wave tiles and the tap-fastest k order, the centre-tap k tile of channel
-// block cb holds exactly input[m][cb*64 .. cb*64+63] for the tile's pixels,
+// Residual layers add the layer input itself (cin == cout).  In halo mode with
+// 64-channel wave tiles and the tap-fastest k order, channel block cb of the
+// halo image holds exactly input[m][cb*64 .. cb*64+63] for the tile's pixels,
 // i.e. the residual of the waves whose channels are block cb: those waves add
-// it to their accumulators from LDS, and the epilogue reads no residual from
-// HBM (the epilogues of all workgroups run at once and are bandwidth-bound).
+// it to their accumulators from LDS at the centre tap, and the epilogue reads
+// no residual from HBM (the epilogues of all workgroups run at once and are
+// bandwidth-bound).  The other tiles add it in the epilogue, all of them: which
+// of them a layer takes depends on the launch's replicas, and a replica's bits
+// must not.
 #include <utility>
 
 #include "runtime.h"
@@ -560,7 +563,7 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
 #pragma unroll
       for (int kg = 0; kg < 2; ++kg) xb[kg] = wb + xa[kg];
     }
-    const bool add_res = a.res_lds && kt == res_kt;
+    const bool add_res = HALO && a.res_lds && kt == res_kt;
 #pragma unroll
     for (int t = 0; t < TPK; ++t) {
       uint32_t wbt = wb;  // this tap's weight sub-stage
@@ -596,18 +599,15 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
     }  // taps of the k tile
     if (add_res) {
       // residual of fragment (tm, tn): 4 channels tn*16 + lg*4 .. +3 of the
-      // block at pixel row wm*TM*16 + tm*16 + li of the centre-tap A tile
-      // (halo mode: image row wm*TM + tm, column li, at halo row + 1, + 1)
+      // block at image row wm*TM + tm, column li (halo row + 1, + 1)
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm) {
         u32x2 rv[TN];
-        const int row = wm * TM * 16 + tm * 16 + li;
         const int hrow = (wm * TM + tm + 1) * halo::HP + li + 1;
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn) {
           const int ch = tn * 2 + (lg >> 1);  // 16-byte chunk of the row
-          const uint32_t ad = HALO ? xst + (uint32_t)(hrow * 128 + ((ch ^ hswz(li + 1)) * 16) + (lg & 1) * 8)
-                                   : wb + (uint32_t)(row * ROW + ((ch ^ swz(row)) * 16) + (lg & 1) * 8);
+          const uint32_t ad = xst + (uint32_t)(hrow * 128 + ((ch ^ hswz(li + 1)) * 16) + (lg & 1) * 8);
           asm volatile("ds_read_b64 %0, %1" : "=v"(rv[tn]) : "v"(ad));
         }
         // the values are produced at the wait: keep every use after it
@@ -987,10 +987,11 @@ hipError_t launch_conv_lds(const ConvArgs &a, hipStream_t s, std::string *label)
   const FastDiv fw = make_fastdiv(a.W), fh = make_fastdiv(a.H), fc = make_fastdiv(a.Csrc);
   const dim3 g((uint32_t)MT * NT * a.C);
   // residual from the staged centre tap: residual == input, tap-fastest k
-  // order (input channels a multiple of the k tile), 64-channel wave tiles
+  // order, 64-channel wave tiles.  Only where the layer's shape alone gives the
+  // tile: the place where a residual is added rounds differently, and the tiles
+  // of other images are chosen by the launch's replicas.
   ConvArgs b = a;
-  b.res_lds = (a.res != nullptr && a.res == a.src && a.taps == 9 && a.Csrc % BK == 0 && a.Csrc == a.N &&
-               (bn == 256 || bn == 128)) ? 1 : 0;
+  b.res_lds = (img16 && a.res != nullptr && a.res == a.src && a.Csrc == a.N && (bn == 256 || bn == 128)) ? 1 : 0;
   // the input gradient on 64-wide halo tiles: 8 waves, one halo buffer
   const bool use_h64 = use_halo64 && a.epi == EPI_DGRAD;
   if (label) {

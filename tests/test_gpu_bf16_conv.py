@@ -1,6 +1,7 @@
 """bf16 convolutions against the oracle, at the sizes where their kernels can go
 wrong: the k loop unrolled over whole 64-channel blocks (k_conv_lds.hip, 128 x
 64 tiles) and the weight gradient of images of any width (k_conv.hip)."""
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -8,6 +9,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from gcpsl_inputs import get_config  # noqa: E402
+from paper_2609_29395_amd import driver  # noqa: E402
 from test_gpu_parity import check_run, matched_run  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +55,22 @@ def test_weight_gradient_of_any_width(H, W, B, w1, w2, w3):
                      dtype="bf16")
     ctx, o, theta0, losses, _ = matched_run(cfg, 1)
     check_run(ctx, o, theta0, losses, cfg)
+
+
+# residual layers whose tile depends on the launch's replicas: eight clusters
+# take 256 x 128 (or 256 x 256) tiles, one alone 128 x 64
+@pytest.mark.parametrize("side,B,w", [(32, 16, 128), (8, 128, 256), (8, 256, 256)])
+def test_serial_residual_layers_bit_for_bit(side, B, w):
+    layers = [("conv", 3, 64, False), ("conv", 64, w, False), ("conv", w, w, True), ("avgpool",), ("linear", w, 4)]
+    cfg = get_config("tiny", H=side, W=side, B=B, C=8, K=64, N_ex=4 * 8 * B, layers=layers, cut=2, momentum=0.9, F=0,
+                     T=1, dtype="bf16")
+    out = []
+    for serial in (False, True):
+        ctx, _ = driver.setup(cfg, max_steps=1)
+        losses = torch.zeros(1, 8, device="cuda")
+        driver.train(ctx, 1, losses=losses, serial=serial)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (losses, ctx.theta, ctx.mom)])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
