@@ -22,10 +22,12 @@ def _cfg(B, C, ch, classes, dtype, **kw):
 
 # batches of one part (8), of a last part of one example (9, 57), of eight
 # parts (64, 100); 16 classes or fewer in registers, more or more than 256
-# channels in LDS; parts limited by the room (40 classes beside few weights)
+# channels in LDS, with eight lanes per logit (up to 128 logits a part) or a
+# thread; parts limited by the room (40 classes beside few weights)
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("B,C,ch,classes", [(8, 2, 16, 4), (9, 2, 64, 10), (57, 1, 136, 7), (100, 2, 256, 16), (64, 3, 24, 17),
-                                            (33, 2, 512, 10), (40, 1, 8, 40)])
+                                            (33, 2, 512, 10), (40, 1, 8, 40), (8, 1, 72, 16), (16, 2, 264, 16),
+                                            (9, 1, 264, 30)])
 def test_round_against_the_oracle(dtype, B, C, ch, classes):
     from test_gpu_parity import check_run, matched_run
     cfg = _cfg(B, C, ch, classes, dtype, T=2, label_smoothing=0.1)
