@@ -26,10 +26,10 @@
 // and keeps the example in registers between the sums and the result where it
 // fits; a few examples that don't take the result in a second launch over the
 // chip.  Batch norm of up to kBnPixels pixels per replica is one launch each
-// way too: a workgroup takes a few channels of every pixel and reads them
-// twice (from L2).  Larger batch norms reduce chunks of pixels, finish the
-// sums and apply them in three launches; their chunks shrink for small
-// tensors (16 to 256 pixels) so that the launches still spread over the chip.
+// way too: a workgroup takes a few channels of every pixel and holds them.
+// Larger batch norms reduce chunks of pixels, finish the sums and apply them in
+// three launches; their chunks shrink for small tensors (16 to 256 pixels) so
+// that the launches still spread over the chip.
 #include "runtime.h"
 
 namespace {
@@ -457,12 +457,12 @@ group_bwd_kernel(NormArgs a, int per) {
 // Batch norm of few pixels: a workgroup of 1024 threads takes SV vectors of
 // channels of every pixel of its replica and holds them (NV vectors per
 // thread), MODE 0 forward (statistics, running state, output), MODE 1 backward
-// (dgamma, dbeta, dz).  NV = 0 reads them twice (from L2).
+// (dgamma, dbeta, dz).
 constexpr int kBnThreads = 1024;
 template <typename T, int SV, int MODE, int NV>
 __global__ void __launch_bounds__(kBnThreads)
 batch_norm_kernel(NormArgs a) {
-  constexpr int VEC = ElemT<T>::VEC, NT = kBnThreads, PL = NT / SV, N = NV > 0 ? NV : 1;
+  constexpr int VEC = ElemT<T>::VEC, NT = kBnThreads, PL = NT / SV;
   __shared__ LaneSums<VEC, NT, SV * VEC> ls;
   // the workgroups that share cache lines (neighbouring channels) on one XCD
   const uint32_t t = xcd_swizzle(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
@@ -487,7 +487,7 @@ batch_norm_kernel(NormArgs a) {
     if (MODE == 1) v.g = load16(du + (int64_t)p * a.Ch);
     return v;
   };
-  auto add = [&](const Pair<T> &v, int) {
+  auto add = [&](const Pair<T> &v) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       const float x = ElemT<T>::to_f(v.x.v[e]);
@@ -501,25 +501,21 @@ batch_norm_kernel(NormArgs a) {
       }
     }
   };
-  V16<T> hx[N], hg[MODE == 1 ? N : 1];
-  if (NV > 0) {
+  V16<T> hx[NV], hg[MODE == 1 ? NV : 1];
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-      if (pl + i * PL < M) {
-        const Pair<T> v = get(pl + i * PL);
-        hx[i] = v.x;
-        if (MODE == 1) hg[MODE == 1 ? i : 0] = v.g;
-      }
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-      if (pl + i * PL < M) add(Pair<T>{hx[i], hg[MODE == 1 ? i : 0]}, 0);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      opaque(hx[i]);
-      if (MODE == 1) opaque(hg[MODE == 1 ? i : 0]);
+  for (int i = 0; i < NV; ++i)
+    if (pl + i * PL < M) {
+      const Pair<T> v = get(pl + i * PL);
+      hx[i] = v.x;
+      if (MODE == 1) hg[MODE == 1 ? i : 0] = v.g;
     }
-  } else {
-    stream_pixels<4>(pl, PL, M, get, add);
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (pl + i * PL < M) add(Pair<T>{hx[i], hg[MODE == 1 ? i : 0]});
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    opaque(hx[i]);
+    if (MODE == 1) opaque(hg[MODE == 1 ? i : 0]);
   }
   ls.reduce(s0, s1, SV, PL);
   const double n = (double)M;
@@ -572,23 +568,12 @@ batch_norm_kernel(NormArgs a) {
     }
     store16(out + (int64_t)p * a.Ch, o);
   };
-  if (NV > 0) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int p = pl + i * PL;
-      if (p < M)
-        put(Pair<T>{hx[i], MODE == 1 ? hg[MODE == 1 ? i : 0]
-                                     : (res ? load16(res + (int64_t)p * a.Ch) : V16<T>{})}, p);
-    }
-  } else {
-    stream_pixels<4>(
-        pl, PL, M,
-        [&](int p) {
-          Pair<T> v = get(p);
-          if (MODE == 0 && res) v.g = load16(res + (int64_t)p * a.Ch);
-          return v;
-        },
-        put);
+  for (int i = 0; i < NV; ++i) {
+    const int p = pl + i * PL;
+    if (p < M)
+      put(Pair<T>{hx[i], MODE == 1 ? hg[MODE == 1 ? i : 0]
+                                   : (res ? load16(res + (int64_t)p * a.Ch) : V16<T>{})}, p);
   }
 }
 
@@ -768,27 +753,28 @@ template <typename T> constexpr int kHoldBwd = ElemT<T>::VEC == 4 ? 16 : 8;
 // and 20 us backward however small the tensor (4 replicas of 64 examples, bf16:
 // 512 channels of 4 x 4 9 / 12 us instead of 17 / 20, 256 channels of 8 x 8
 // 18 / 24 instead of 24 / 30).
-constexpr int64_t kBnPixels = 8192;
+constexpr int kBnHold = 8;  // pixels that a thread holds at most
+constexpr int64_t kBnPixels = kBnHold * kBnThreads;
 
 template <typename T> bool bn_one_launch(const NormArgs &a) {
   return a.groups == 0 && (int64_t)a.Bt * a.H * a.W <= kBnPixels;
 }
 template <typename T, int SV, int MODE> void run_bn_sv(const NormArgs &a, hipStream_t s) {
   const dim3 grid(a.Ch / ElemT<T>::VEC / SV, a.C);
-  const int nv = (a.Bt * a.H * a.W + kBnThreads / SV - 1) / (kBnThreads / SV);
-  if (nv <= 2)
+  if (a.Bt * a.H * a.W <= 2 * kBnThreads / SV)
     hipLaunchKernelGGL((batch_norm_kernel<T, SV, MODE, 2>), grid, dim3(kBnThreads), 0, s, a);
-  else if (nv <= 8)
-    hipLaunchKernelGGL((batch_norm_kernel<T, SV, MODE, 8>), grid, dim3(kBnThreads), 0, s, a);
   else
-    hipLaunchKernelGGL((batch_norm_kernel<T, SV, MODE, 0>), grid, dim3(kBnThreads), 0, s, a);
+    hipLaunchKernelGGL((batch_norm_kernel<T, SV, MODE, kBnHold>), grid, dim3(kBnThreads), 0, s, a);
 }
 template <typename T, int MODE> void run_bn(const NormArgs &a, hipStream_t s) {
   // (the fp64 sums bound a workgroup: two vectors each only where that still
   // gives 128 of them in a launch of all the context's replicas; a launch of
-  // fewer takes the same slices, whose pixel lanes set the order of the sums)
+  // fewer takes the same slices, whose pixel lanes set the order of the sums.
+  // And only where a thread still holds its pixels: read twice, 256 channels of
+  // 8,192 pixels took 119 us of 4 fp32 replicas and 103 of 8 bf16 ones, where one
+  // vector each takes 68 and 75)
   const int CV = a.Ch / ElemT<T>::VEC;
-  if (CV % 2 == 0 && CV / 2 * a.Call >= 128)
+  if (CV % 2 == 0 && CV / 2 * a.Call >= 128 && a.Bt * a.H * a.W <= kBnHold * kBnThreads / 2)
     run_bn_sv<T, 2, MODE>(a, s);
   else
     run_bn_sv<T, 1, MODE>(a, s);
