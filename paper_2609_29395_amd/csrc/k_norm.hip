@@ -25,7 +25,7 @@
 // workgroup takes whole examples, so it has every value of its statistics,
 // and keeps the example in registers between the sums and the result where it
 // fits; a few examples that don't take the result in a second launch over the
-// chip.  Batch norm of up to kBnPixels pixels per replica is one launch each
+// chip.  Batch norm of few pixels (bn_one_launch) is one launch each
 // way too: a workgroup takes a few channels of every pixel and holds them.
 // Larger batch norms reduce chunks of pixels, finish the sums and apply them in
 // three launches; their chunks shrink for small tensors (16 to 256 pixels) so
@@ -747,17 +747,31 @@ bool group_split(const NormArgs &a, int CV, int most) {
 constexpr int kHoldFwd = 16;
 template <typename T> constexpr int kHoldBwd = ElemT<T>::VEC == 4 ? 16 : 8;
 
-// Pixels per replica up to which a batch norm runs in one launch: its time is
-// that of one workgroup (M pixels x 32 bytes, read twice and written once at
-// a CU's rate, and the fp64 sums), while the three launches cost 17 us forward
-// and 20 us backward however small the tensor (4 replicas of 64 examples, bf16:
-// 512 channels of 4 x 4 9 / 12 us instead of 17 / 20, 256 channels of 8 x 8
-// 18 / 24 instead of 24 / 30).
+// Pixels per replica up to which a batch norm runs in one launch.  Its time is
+// that of one workgroup (M pixels at a CU's rate and the fp64 sums), whatever
+// the replicas, while the three launches' grows with all of them from 28 us
+// forward and backward.  Rows of more than 64 bytes cost the workgroup more: it
+// takes 16 bytes of every line.  Forward and backward, us, one launch / three:
+//                             4,096        6,144        8,192 pixels
+//   fp32,  16 channels, 1   22 / 29      27 / 31      32 / 34
+//          64 channels, 1   29 / 30      38 / 33      47 / 36   of 1 replica
+//                       4   28 / 32      36 / 38      45 / 42   of 4
+//   bf16,  64 channels, 1   33 / 33      43 / 35      54 / 39
+//                       4   31 / 39      39 / 49      48 / 54
+//                       3   33 / 36      44 / 44      55 / 51
+// So wide rows may have more pixels with every replica of the context, by the
+// points where the two times meet, up to what a thread holds (fp32, whose rows
+// are twice as long: fewer).
 constexpr int kBnHold = 8;  // pixels that a thread holds at most
-constexpr int64_t kBnPixels = kBnHold * kBnThreads;
+constexpr int kBnPixels = kBnHold * kBnThreads, kBnPixelsWide = 4096;
 
 template <typename T> bool bn_one_launch(const NormArgs &a) {
-  return a.groups == 0 && (int64_t)a.Bt * a.H * a.W <= kBnPixels;
+  const int64_t M = (int64_t)a.Bt * a.H * a.W;
+  if (a.groups != 0 || M > kBnPixels) return false;
+  if (a.Ch * sizeof(T) <= 64) return true;
+  const int64_t more = a.Call - 1;
+  return M <= (sizeof(T) == 4 ? std::min<int64_t>(kBnPixelsWide + 768 * more, 7168)
+                              : std::min<int64_t>(kBnPixelsWide + 1366 * more, kBnPixels));
 }
 template <typename T, int SV, int MODE> void run_bn_sv(const NormArgs &a, hipStream_t s) {
   const dim3 grid(a.Ch / ElemT<T>::VEC / SV, a.C);

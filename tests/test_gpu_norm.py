@@ -34,13 +34,14 @@ def test_serial_clusters_of_large_norm_layers_bit_for_bit(dtype):
 # x 72 channels, and 520), by their own workgroup or where they are fewer than 64
 # by an elementwise pass; 3 vectors per pixel (idle lanes); two channels per
 # group and one group; batch norm: one launch of up to 2 and 8 pixels a thread,
-# three launches, one and two vectors per workgroup
+# three launches (more than 8,192 pixels, or 4,096 of wide rows), one and two
+# vectors per workgroup
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("side,B,C,w1,g1,w2,g2,w3", [
     (5, 7, 2, 8, 4, 24, 1, 40), (9, 3, 1, 24, 3, 64, 32, 8), (16, 5, 2, 64, 32, 128, 32, 16), (32, 2, 1, 72, 9, 8, 2, 24),
     (16, 33, 2, 8, 2, 16, 4, 136), (32, 9, 1, 8, 4, 8, 1, 8), (3, 5, 16, 8, 2, 16, 4, 256),
     (2, 33, 2, 520, 8, 16, 4, 8), (3, 9, 2, 520, 1, 1016, 127, 8),
-    (16, 17, 2, 8, 2, 8, 2, 1024),
+    (16, 17, 2, 8, 2, 8, 2, 1024), (16, 17, 1, 8, 2, 8, 2, 40),
 ])
 def test_norm_round_against_the_oracle(dtype, side, B, C, w1, g1, w2, g2, w3):
     from test_gpu_parity import check_run, matched_run
