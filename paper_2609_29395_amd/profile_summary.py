@@ -44,20 +44,9 @@ SIMDS = 256 * 4  # MI355X: 256 compute units of 4 SIMDs
 
 def kernel_label(name: str) -> str:
     """rocprof's demangled name -> the label gcpsl_timing reports."""
-    m = re.search(r"conv_kernel<(unsigned short|float), (\d+), (\d+), (\d+), (\d+), (true|false), (\d), "
-                  r"(\d+), (\d+), (\d+)>", name)
+    m = re.search(r"\bwgrad_kernel<(\d+), (\d+), (true|false)>", name)
     if m:
-        t = "bf16" if m.group(1) == "unsigned short" else "f32"
-        kind = "conv_fwd" if m.group(7) == "0" else "conv_dgrad"
-        w = int(m.group(4)) * int(m.group(5))
-        k = int(m.group(9)) // (2 if t == "bf16" else 4)
-        return (f"{kind}<{t},{m.group(2)}x{m.group(3)}x{k},w{w},"
-                f"{'vec' if m.group(6) == 'true' else 'gather'}>")
-    m = re.search(r"wgrad_kernel<(unsigned short|float), (\d+), (\d+), (\d+), (\d+), (true|false)>", name)
-    if m:
-        t = "bf16" if m.group(1) == "unsigned short" else "f32"
-        w = int(m.group(4)) * int(m.group(5))
-        return f"conv_wgrad<{t},{m.group(2)}x{m.group(3)},w{w},{'vec' if m.group(6) == 'true' else 'gather'}>"
+        return f"conv_wgrad<bf16,{m.group(1)}x{m.group(2)},w4,{'vec' if m.group(3) == 'true' else 'anywidth'}>"
     m = re.search(r"conv_f32_(halo_)?kernel<(\d+), (\d+), (\d+), (\d+), (\d)(, \d)?(, true)?", name)
     if m:  # fp32 on the bf16 matrix cores
         kind = "conv_fwd" if m.group(6) == "0" else "conv_dgrad"

@@ -64,6 +64,13 @@ def test_image_layer_labels():
     assert ps.kernel_label(ns + "conv_img_dgrad_kernel(ConvArgs, int, int)") == "conv_dgrad<bf16,256x32x576,w8,img,pool>"
 
 
+@pytest.mark.parametrize("flag,mode", [("true", "vec"), ("false", "anywidth")])
+def test_general_weight_gradient_labels(flag, mode):
+    # (pixel blocks within an image row, or of any width)
+    label = ps.kernel_label(f"void (anonymous namespace)::wgrad_kernel<64, 128, {flag}>(WgradArgs, FastDiv)")
+    assert label == f"conv_wgrad<bf16,64x128,w4,{mode}>" and ps.kernel_source(label) == "k_conv.hip"
+
+
 @pytest.mark.parametrize("label,source", [
     ("conv_fwd<bf16,256x128x64,w8,halo1>", "k_conv_lds.hip"),
     ("conv_dgrad<bf16,256x128x64,w8,halo1>", "k_conv_lds.hip"),
