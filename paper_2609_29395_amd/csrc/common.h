@@ -61,6 +61,27 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv &f) {
   return (uint32_t)(((uint64_t)__umulhi(n, f.m) + n) >> f.s);
 }
 
+// ---------------------------------------------------------- buffer access
+// An offset at or beyond the descriptor's byte count reads zero without
+// touching memory.  Invalid lanes use kOob (a replica's layer tensors are below
+// 2 GiB), so zero padding and ragged tiles need no branches.
+constexpr uint32_t kOob = 0x80000000u;
+constexpr int kBufferFlags = 0x00020000;  // raw 32-bit data format
+
+// The descriptor must live in scalar registers; base and size are uniform
+// across the workgroup, readfirstlane makes that explicit to the compiler.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  void *q = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), kBufferFlags);
+}
+
+__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0));
+}
+
 // ----------------------------------------------------- XCD-aware tile order
 // Workgroups are dealt to the 8 XCDs round-robin by linear id.  Map linear id
 // L to logical tile so that each XCD walks a contiguous run of logical tiles

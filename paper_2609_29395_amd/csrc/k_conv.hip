@@ -33,26 +33,6 @@ struct Pack {
   bf16_t v[8];
 };
 
-// Raw buffer access: an offset at or beyond the descriptor's byte count reads
-// zero without touching memory.  Invalid lanes use kOob (tensors here are
-// far below 2 GiB), so zero padding and ragged tiles need no branches.
-constexpr uint32_t kOob = 0x80000000u;
-constexpr int kBufferFlags = 0x00020000;  // raw 32-bit data format
-
-// The descriptor must live in scalar registers; base and size are uniform
-// across the workgroup, readfirstlane makes that explicit to the compiler.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void *base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  void *q = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), kBufferFlags);
-}
-
-__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-}
-
 // Tile geometry and the MFMA loop over one staged k tile, one k group at a time
 // (few registers).
 template <int BM, int BN, int WM, int WN> struct Tile {
@@ -193,7 +173,7 @@ wgrad_kernel(WgradArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int 
         const int c0 = m0 + rowb[it] * VEC;
         const uint32_t o0 = c0 < a.Co ? ((uint32_t)pbase * (uint32_t)a.Co + (uint32_t)c0) * ESZ : kOob;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) reg[it][e] = buffer_load16(rsg, o0 + (uint32_t)(e * a.Co) * ESZ, 0);
+        for (int e = 0; e < VEC; ++e) reg[it][e] = buffer_load16(rsg, o0 + (uint32_t)(e * a.Co) * ESZ);
         continue;
       }
       if constexpr (VB) {
@@ -201,7 +181,7 @@ wgrad_kernel(WgradArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int 
           // im2col rows: contiguous pixels, like the gradient operand
           const uint32_t o0 = bvalid[it] ? ((uint32_t)pbase * (uint32_t)a.Ci + (uint32_t)bc[it]) * ESZ : kOob;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) reg[it][e] = buffer_load16(rsx, o0 + (uint32_t)(e * a.Ci) * ESZ, 0);
+          for (int e = 0; e < VEC; ++e) reg[it][e] = buffer_load16(rsx, o0 + (uint32_t)(e * a.Ci) * ESZ);
         } else if (kind[it] == 1) {
           const uint32_t q1 = fdiv((uint32_t)pbase, fd_w);
           const int w0 = (int)((uint32_t)pbase - q1 * (uint32_t)a.W);
@@ -215,7 +195,7 @@ wgrad_kernel(WgradArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int 
             bool ok = rowok;
             if (e == 0) ok = ok && (w0 + bs[it] - 1 >= 0);
             if (e == VEC - 1) ok = ok && (w0 + VEC - 1 + bs[it] - 1 < a.W);
-            reg[it][e] = buffer_load16(rsx, ok ? (uint32_t)(base + e * a.Ci) * ESZ : kOob, 0);
+            reg[it][e] = buffer_load16(rsx, ok ? (uint32_t)(base + e * a.Ci) * ESZ : kOob);
           }
         } else {
 #pragma unroll
@@ -231,7 +211,7 @@ wgrad_kernel(WgradArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, int 
           const bool ok = kind[it] == 1 && bvalid[it] && pbase + e < p_end &&
                           (unsigned)(h + br[it] - 1) < (unsigned)a.H && (unsigned)(w + bs[it] - 1) < (unsigned)a.W;
           reg[it][e] = buffer_load16(
-              rsx, ok ? (uint32_t)((pbase + e + shift) * a.Ci + bc[it]) * ESZ : kOob, 0);
+              rsx, ok ? (uint32_t)((pbase + e + shift) * a.Ci + bc[it]) * ESZ : kOob);
           if (++w == a.W) {
             w = 0;
             if (++h == a.H) h = 0;

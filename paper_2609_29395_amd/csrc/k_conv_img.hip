@@ -37,9 +37,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-constexpr uint32_t kOob = 0x80000000u;
-constexpr int kBufferFlags = 0x00020000;
-
 constexpr int IMG = 32;                    // image side
 constexpr int HP = IMG + 2;                // halo row width
 constexpr int NTHR = 512;                  // 8 waves: wave w computes image rows RPW w .. RPW w + RPW - 1
@@ -64,14 +61,6 @@ template <int CS, int NO, int RPW = 1> struct ImgCfg {
   static_assert(W_BYTES % 1024 == 0 && WCH % 8 == 0, "weight rows in whole 1 KB copies, 8-chunk groups");
   static constexpr bool FITS2 = 2 * LDS <= 160 * 1024;  // two workgroups per CU
 };
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  void *q = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), kBufferFlags);
-}
 
 __device__ __forceinline__ void mma(f32x4_t &acc, const u32x4 &a, const u32x4 &b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
@@ -108,8 +97,8 @@ conv_img_kernel(ConvArgs a, int MT) {
   u32x2 cv[CF::HQ];
   int kw[CF::HQ];
   {
-    const __amdgpu_buffer_rsrc_t rss = rsrc(src, (uint32_t)((int64_t)M * CS * 2));
-    const __amdgpu_buffer_rsrc_t rsw = rsrc(wt, (uint32_t)CF::W_BYTES);
+    const __amdgpu_buffer_rsrc_t rss = make_rsrc(src, (uint32_t)((int64_t)M * CS * 2));
+    const __amdgpu_buffer_rsrc_t rsw = make_rsrc(wt, (uint32_t)CF::W_BYTES);
     const uint8_t *cd = pooled ? a.pool_code + rep * a.src_rs : nullptr;
     const int img0 = m0 / (IMG * IMG) * (IMG / 2) * (IMG / 2);  // first pooled pixel of the tile's image
 #pragma unroll
@@ -476,8 +465,8 @@ conv_img_pool_kernel(ConvArgs a, int MT, int WPR) {
   const int M = a.Bt * IMG * IMG;
   const bf16_t *src = reinterpret_cast<const bf16_t *>(a.src) + rep * a.src_rs;
   const bf16_t *wt = reinterpret_cast<const bf16_t *>(a.wt) + rep * a.wt_rs;
-  const __amdgpu_buffer_rsrc_t rss = rsrc(src, (uint32_t)((int64_t)M * CS * 2));
-  const __amdgpu_buffer_rsrc_t rsw = rsrc(wt, (uint32_t)CF::W_BYTES);
+  const __amdgpu_buffer_rsrc_t rss = make_rsrc(src, (uint32_t)((int64_t)M * CS * 2));
+  const __amdgpu_buffer_rsrc_t rsw = make_rsrc(wt, (uint32_t)CF::W_BYTES);
 
   // the weight matrix, once, by all 16 waves: row n at n * 656 bytes, its
   // 40 chunks in order and a zero one
@@ -744,7 +733,7 @@ conv_img_dgrad_kernel(ConvArgs a, int MT, int WPR) {
   const bf16_t *wt = reinterpret_cast<const bf16_t *>(a.wt) + rep * a.wt_rs;
   const bf16_t *msk = reinterpret_cast<const bf16_t *>(a.mask) + rep * a.out_rs;
   bf16_t *out = reinterpret_cast<bf16_t *>(a.out) + rep * a.out_rs;
-  const __amdgpu_buffer_rsrc_t rsw = rsrc(wt, (uint32_t)CF::W_BYTES);
+  const __amdgpu_buffer_rsrc_t rsw = make_rsrc(wt, (uint32_t)CF::W_BYTES);
 
   // the weight matrix, once, by all 16 waves: row n at n * 1168 bytes, its
   // 72 chunks in order and a zero one

@@ -50,8 +50,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BK = 64;
 constexpr int ROW = BK * 2;  // bytes per LDS row
-constexpr uint32_t kOob = 0x80000000u;
-constexpr int kBufferFlags = 0x00020000;
 
 template <int BM_, int BN, int WM, int WN, int PFO = 0, int NST = 2> struct Cfg {
   static constexpr int BM = BM_, BN_ = BN;
@@ -113,14 +111,6 @@ __device__ __forceinline__ int hswz(int wp) { return wp & 7; }
 
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int wn_of(int wave, int WN) { return wave % WN; }
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  void *q = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), kBufferFlags);
-}
 
 __device__ __forceinline__ void mma(f32x4_t &acc, const u32x4 &a, const u32x4 &b) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
@@ -192,8 +182,8 @@ template <typename CF, bool TAPS1>
 __device__ __forceinline__ void issue_tile(int kt, char *stage0, int wave, const ConvArgs &a, FastDiv fd_c,
                                            const void *src, const void *wt, const int *achunk, const int *arowoff,
                                            const uint32_t *amask, const uint32_t *boff) {
-  const __amdgpu_buffer_rsrc_t rsa = rsrc(src, (uint32_t)(a.src_rs * 2));
-  const __amdgpu_buffer_rsrc_t rsb = rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(src, (uint32_t)(a.src_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsb = make_rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
   char *sa = stage0 + (kt & 1) * CF::STAGE;
   int kcol = kt * BK;  // first weight column of the tile
   if (!TAPS1 && a.Csrc % BK == 0) {
@@ -243,8 +233,8 @@ __device__ __forceinline__ void issue_tile(int kt, char *stage0, int wave, const
 template <typename CF, int U>
 __device__ __forceinline__ void issue_unrolled(char *stage0, const ConvArgs &a, const void *src, const void *wt,
                                                const uint32_t *aoff, const uint32_t *boff, uint32_t ca, uint32_t cw) {
-  const __amdgpu_buffer_rsrc_t rsa = rsrc(src, (uint32_t)(a.src_rs * 2));
-  const __amdgpu_buffer_rsrc_t rsb = rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(src, (uint32_t)(a.src_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsb = make_rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
   char *sa = stage0 + (U % 3) * CF::STAGE;
 #pragma unroll
   for (int q = 0; q < CF::SA; ++q)
@@ -271,7 +261,7 @@ __device__ __forceinline__ void unroll_steps(S &step, std::integer_sequence<int,
 template <int NTHR, int HB>
 __device__ __forceinline__ void issue_halo_piece(int q, int cb, char *smem, int wave, const ConvArgs &a,
                                                  const void *src, int img_off, int hoff) {
-  const __amdgpu_buffer_rsrc_t rsa = rsrc(src, (uint32_t)(a.src_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsa = make_rsrc(src, (uint32_t)(a.src_rs * 2));
   if (q * NTHR * 16 + wave * 1024 < halo::BYTES) {
     const uint32_t off = hoff >= 0 ? (uint32_t)(img_off + hoff + cb * BK) * 2u : kOob;
     const int buf = HB == 2 ? (cb & 1) : 0;
@@ -286,7 +276,7 @@ __device__ __forceinline__ void issue_halo_piece(int q, int cb, char *smem, int 
 template <typename CF, int TPK, int HB>
 __device__ __forceinline__ void issue_weights(int kt, char *smem, int wave, const ConvArgs &a, const void *wt,
                                               const uint32_t *boff) {
-  const __amdgpu_buffer_rsrc_t rsb = rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
+  const __amdgpu_buffer_rsrc_t rsb = make_rsrc(wt, (uint32_t)((int64_t)a.N * a.Kp * 2));
   constexpr int KPB = 9 / TPK;  // k tiles per channel block
   const int cb = kt / KPB, kr = kt - KPB * cb;
   char *sb = smem + HB * halo::BYTES + (kt & 1) * TPK * CF::B_BYTES + wave * 1024;
@@ -648,8 +638,8 @@ conv_lds_kernel(ConvArgs a, FastDiv fd_w, FastDiv fd_h, FastDiv fd_c, int MT, in
     const int q1 = (int)fdiv((uint32_t)m, fd_w);
     return (int64_t)(2 * q1 + cls.y) * (2 * a.W) + 2 * (m - q1 * a.W) + cls.x;
   };
-  const __amdgpu_buffer_rsrc_t rsr = rsrc(res ? res : out, (uint32_t)(a.out_rs * 2));
-  const __amdgpu_buffer_rsrc_t rsm = rsrc(msk ? msk : out, (uint32_t)(a.out_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsr = make_rsrc(res ? res : out, (uint32_t)(a.out_rs * 2));
+  const __amdgpu_buffer_rsrc_t rsm = make_rsrc(msk ? msk : out, (uint32_t)(a.out_rs * 2));
   // dgrad: the mask loads of every pass are issued up front, so their HBM
   // latency is paid once per tile instead of once per pass
   float avs[8];  // AVG: this lane's sums of its 8 channels over its pixel rows (or windows)

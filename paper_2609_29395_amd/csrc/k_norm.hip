@@ -211,7 +211,7 @@ template <int VEC, int NT, int MAXC> struct LaneSums {
     int lgS = 0;
     while ((2 << lgS) * O <= NT && lgS < 6) ++lgS;
     const int S = 1 << lgS, seg = tid & (S - 1);
-    for (int o = tid >> lgS; o < O; o += NT >> lgS) {  // (whole waves leave together: O S is a multiple of 64, or S = 1)
+    for (int o = tid >> lgS; o < O; o += NT >> lgS) {  // (the S threads of an output share o: they leave together)
       const int c = o >> 1, k = o & 1;
       const int cc = c / VEC, at = k * VEC + c % VEC;
       double t = 0.0;

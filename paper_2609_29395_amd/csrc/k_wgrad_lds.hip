@@ -37,8 +37,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
 
-constexpr uint32_t kOob = 0x80000000u;
-constexpr int kBufferFlags = 0x00020000;
 constexpr int kDead = 1 << 30;  // row index that fails every pixel test
 
 // BK pixels per k tile (a multiple of the 32 of one MFMA k group), NST LDS
@@ -82,14 +80,6 @@ __device__ __forceinline__ int swz(int row) {
   else return (((row >> 1) & 1) | ((row >> 2) & 2)) << 1;
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  void *q = reinterpret_cast<void *>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(q, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), kBufferFlags);
-}
-
 // One operand fragment: 8 pixels (two transposing reads 4 pixel rows apart).
 template <int OFF, int ROW>
 __device__ __forceinline__ void read_frag(u32x4 &f, uint32_t addr) {
@@ -113,8 +103,8 @@ template <typename CF, bool TAPS1>
 __device__ __forceinline__ void issue_tile(int kt, char *stage0, const WgradArgs &a, FastDiv fd_w, FastDiv fd_h,
                                            const void *G, const void *X, int M, int p_begin, int p_end,
                                            int arow, int acol, int brow, int bci, int btap) {
-  const __amdgpu_buffer_rsrc_t rsg = rsrc(G, (uint32_t)((int64_t)M * a.Co * 2));
-  const __amdgpu_buffer_rsrc_t rsx = rsrc(X, (uint32_t)((int64_t)M * a.Ci * 2));
+  const __amdgpu_buffer_rsrc_t rsg = make_rsrc(G, (uint32_t)((int64_t)M * a.Co * 2));
+  const __amdgpu_buffer_rsrc_t rsx = make_rsrc(X, (uint32_t)((int64_t)M * a.Ci * 2));
   char *sa = stage0 + (kt % CF::NST) * CF::STAGE;
   const int pt = p_begin + kt * CF::BK;
 #pragma unroll
@@ -355,8 +345,8 @@ template <int NST>
 __device__ __forceinline__ void wh_issue(int kt, char *stage0, const void *G, const void *X, uint32_t gbytes,
                                          uint32_t xbytes, int Co, int Ci, int p_begin, int arow, int acol,
                                          const int (&hrel)[wh::SB], const int (&hh)[wh::SB]) {
-  const __amdgpu_buffer_rsrc_t rsg = rsrc(G, gbytes);
-  const __amdgpu_buffer_rsrc_t rsx = rsrc(X, xbytes);
+  const __amdgpu_buffer_rsrc_t rsg = make_rsrc(G, gbytes);
+  const __amdgpu_buffer_rsrc_t rsx = make_rsrc(X, xbytes);
   char *sa = stage0 + (kt % NST) * wh::STAGE;
   const int pt = p_begin + kt * wh::BK;
 #pragma unroll
@@ -589,8 +579,8 @@ template <int NST, bool POOL>
 __device__ __forceinline__ void wi_issue(int kt, char *smem, int wave, int lane, const void *G, const void *X,
                                          const void *code, uint32_t gbytes, uint32_t xbytes, int p_begin, int arow,
                                          int acol, const int (&hrel)[wi::SB], const int (&hh)[wi::SB]) {
-  const __amdgpu_buffer_rsrc_t rsg = rsrc(G, gbytes);
-  const __amdgpu_buffer_rsrc_t rsx = rsrc(X, xbytes);
+  const __amdgpu_buffer_rsrc_t rsg = make_rsrc(G, gbytes);
+  const __amdgpu_buffer_rsrc_t rsx = make_rsrc(X, xbytes);
   char *st = smem + (kt % NST) * wi::STAGE;
   const int pt = p_begin + kt * wi::BK;
   const int h0 = (pt / wi::IMG) % wi::IMG;  // first image row of the tile
@@ -630,7 +620,7 @@ __device__ __forceinline__ void wi_issue(int kt, char *smem, int wave, int lane,
       const uint32_t off = (uint32_t)(prow * wi::PROW_G + t16);  // wave * 1024 + lane * 16
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsg, LDS_PTR(sb + wi::RAW_G + wave * 1024), 16, off, 0, 0, 0);
     } else if (wave == 2) {
-      const __amdgpu_buffer_rsrc_t rsc = rsrc(code, gbytes / 2);
+      const __amdgpu_buffer_rsrc_t rsc = make_rsrc(code, gbytes / 2);
       const uint32_t off = (uint32_t)(prow * wi::PROW_C + t16 - 2048);  // lane * 16
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsc, LDS_PTR(sb + wi::RAW_C), 16, off, 0, 0, 0);
     } else {
@@ -951,8 +941,8 @@ constexpr int VROW = IMG_W * IMG_C * 2 / 16;  // 16-byte pieces per image row (1
 
 __device__ __forceinline__ void wc_issue(char *dst, const bf16_t *G, const bf16_t *X, uint32_t gbytes,
                                          uint32_t xbytes, int p, int lane) {
-  const __amdgpu_buffer_rsrc_t rsg = rsrc(G, gbytes);
-  const __amdgpu_buffer_rsrc_t rsx = rsrc(X, xbytes);
+  const __amdgpu_buffer_rsrc_t rsg = make_rsrc(G, gbytes);
+  const __amdgpu_buffer_rsrc_t rsx = make_rsrc(X, xbytes);
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const uint32_t off = (uint32_t)(p * wc::ROW + h * 1024 + lane * 16);
@@ -966,8 +956,8 @@ __device__ __forceinline__ void wc_issue(char *dst, const bf16_t *G, const bf16_
 // h + r - 1; lanes past 36 and rows outside the image read zero)
 __device__ __forceinline__ void wc_issue_img3(char *dst, const bf16_t *G, const bf16_t *X, uint32_t gbytes,
                                               uint32_t xbytes, int p, int H, int lane) {
-  const __amdgpu_buffer_rsrc_t rsg = rsrc(G, gbytes);
-  const __amdgpu_buffer_rsrc_t rsx = rsrc(X, xbytes);
+  const __amdgpu_buffer_rsrc_t rsg = make_rsrc(G, gbytes);
+  const __amdgpu_buffer_rsrc_t rsx = make_rsrc(X, xbytes);
 #pragma unroll
   for (int h = 0; h < 2; ++h)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsg, LDS_PTR(dst + h * 1024), 16,
