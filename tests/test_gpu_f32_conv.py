@@ -1,6 +1,6 @@
 """The fp32 convolutions on the bf16 matrix cores (k_conv_f32.hip): every tile
 and both stagings at the sizes where they can go wrong, against the oracle,
-and sums with operands that have no finite three-way split."""
+and sums with operands that have no finite three-way split, in every pass."""
 import numpy as np
 import pytest
 
@@ -9,7 +9,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 from gcpsl_inputs import get_config  # noqa: E402
-from paper_2609_29395_amd import gcpsl  # noqa: E402
+from paper_2609_29395_amd import driver, gcpsl  # noqa: E402
 from test_gpu_parity import check_run, matched_run  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -35,12 +35,40 @@ def test_round_against_the_oracle(side, B, C, widths):
     check_run(ctx, o, theta0, losses, cfg)
 
 
-def _round(images, layers, side, change=None):
-    """One round of one cluster on `images` (all of them, one batch): act0,
-    act1, grad, the batch's example order, labels and parameters."""
+# Tiles of many replicas: 288 pixels end inside every tile, 72, 40 and 24 channels
+# inside the channel tiles and (flat: per-tap staging) the k stages, at the replica
+# counts that just reach the 256 workgroups of each tile's rule
+@pytest.mark.parametrize("C,widths,fwd,dgrad,wgrad", [
+    (128, (32, 72, 32), ["256x128,w8,halo", "256x32,w8,halo"], ["256x128,w8,halo", "256x32,w8,halo"], ["64x288,w4,halo"]),
+    (64, (32, 72, 32), ["128x64,w8,halo", "64x32,w4,halo"], ["128x64,w8,halo", "64x32,w4,halo"], ["64x288,w4,halo"]),
+    (32, (32, 72, 32), ["64x64,w4,halo"], ["64x64,w4,halo"], ["32x32,w4"]),
+    (86, (24, 72, 24), ["128x128,w8", "128x32,w4"], ["128x128,w8", "128x32,w4"], ["32x128,w4"]),
+    (86, (24, 40, 24), ["128x64,w4"], ["128x64,w4"], ["32x32,w4"]),
+    (2, (136, 8, 136), ["64x64,w4", "64x32,w4,halo"], ["32x64,w4,halo", "64x64,w4"], ["128x32,w4", "128x128,w4"]),
+    (2, (40, 24, 8), ["32x32,w4"], ["32x32,w4", "64x64,w4"], ["64x32,w4", "32x128,w4"]),
+])
+def test_every_tile_against_the_oracle(C, widths, fwd, dgrad, wgrad):
+    cfg = get_config("tiny", H=6, W=6, B=8, C=C, K=8 * C, N_ex=128 * C, layers=_net(*widths), cut=2, momentum=0.9,
+                     F=0, T=1, rule="size")
+    ctx, o, theta0, losses, _ = matched_run(cfg, 1)
+    check_run(ctx, o, theta0, losses, cfg)
+    # the tiles the rows are for
+    ctx, _ = driver.setup(cfg, max_steps=1)
+    ctx.timing(True)
+    ctx.sample(0)
+    ctx.step(0)
+    ran = set(ctx.timing_read())
+    want = {f"conv_{k}<f32,{t},split>" for k, ts in (("fwd", fwd), ("dgrad", dgrad), ("wgrad", wgrad)) for t in ts}
+    assert want <= ran, (want - ran, ran)
+
+
+def _round(images, layers, side, change=None, labels=None):
+    """One round of one cluster on `images` (all of them, one batch): the convs'
+    outputs, grad, the batch's example order, labels, parameters and the
+    gradients at the convs' sums."""
     B = len(images)
     rng = np.random.default_rng(3)
-    labels = rng.integers(0, 4, B).astype(np.int32)
+    labels = rng.integers(0, 4, B).astype(np.int32) if labels is None else labels
     shapes = []
     for s in layers:
         if s[0] == "conv":
@@ -58,8 +86,10 @@ def _round(images, layers, side, change=None):
     ctx.step(0)
     torch.cuda.synchronize()
     idx = ctx.tensor("idx").cpu().numpy()
-    acts = [ctx.tensor(f"act{i}").cpu().numpy().reshape(B, side, side, -1) for i in range(2)]
-    return acts, ctx.tensor("grad").cpu().numpy(), idx, labels, theta
+    convs = [i for i, s in enumerate(layers) if s[0] == "conv"]
+    acts, gpre = ([ctx.tensor(f"{n}{i}").cpu().numpy().reshape(B, side, side, -1) for i in convs]
+                  for n in ("act", "gpre"))
+    return acts, ctx.tensor("grad").cpu().numpy(), idx, labels, theta, gpre
 
 
 def _conv(x, w, b):
@@ -84,7 +114,7 @@ def test_infinities_and_nan_pass_as_in_fp32(value):
     side = 8
     images = np.random.default_rng(1).standard_normal((6, side, side, 3)).astype(np.float32)
     images[2, 3, 4, 1] = value
-    (a0, a1), _, idx, _, th = _round(images, LAYERS, side)
+    (a0, a1), _, idx, _, th, _ = _round(images, LAYERS, side)
     w0 = _conv(images[idx].astype(np.float64), th[0], th[1])
     # the second layer from the GPU's own first one
     w1 = _conv(a0.astype(np.float64), th[2], th[3])
@@ -108,7 +138,7 @@ def test_values_that_round_to_infinity_in_bf16():
         th[2] *= np.float32(1e-30)
         th[4] *= np.float32(1e-7)
 
-    (a0, a1), grad, idx, labels, th = _round(images, LAYERS, side, change)
+    (a0, a1), grad, idx, labels, th, _ = _round(images, LAYERS, side, change)
     assert np.isfinite(a0).all() and np.isfinite(a1).all() and a0.max() > 3.39e38
     assert np.allclose(a0, _conv(images[idx].astype(np.float64), th[0], th[1]), rtol=1e-5, atol=1e-5)
     # (360 products of up to 3.4e8 cancel: an element's bound is 360 x 2^-24 of their magnitude)
@@ -149,9 +179,78 @@ def test_sums_of_large_terms_that_cancel():
         th[3][:] = 0
 
     images = np.ones((3, side, side, 3), np.float32)
-    (a0, a1), _, _, _, th = _round(images, layers, side, change)
+    (a0, a1), _, _, _, th, _ = _round(images, layers, side, change)
     assert (a0 == top).all()
     want = _conv(a0.astype(np.float64), th[2], th[3])
     terms = 1.5 * 32 * 9 * float(top)**2
     assert want.max() < float(np.finfo(np.float32).max) < terms
     assert np.isfinite(a1).all() and np.abs(a1 - want).max() <= 576 * 2.0**-24 * terms
+
+
+def _same(got, want):
+    """Infinities and NaN where `want` (float64) has them, the others close."""
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isposinf(got), np.isposinf(want)) and \
+        np.array_equal(np.isneginf(got), np.isneginf(want))
+    fin = np.isfinite(want)
+    if fin.any():
+        assert np.abs(got[fin] - want[fin]).max() <= 1e-5 * max(np.abs(want[fin]).max(), 1e-30)
+
+
+def _grads64(g, x, w):
+    """Weight gradient [co][3][3][ci], bias gradient and input gradient of a conv
+    in float64 (padding as zeros, as on the GPU: an infinity times one is NaN)."""
+    n, h, v, _ = g.shape
+    gp, xp = (np.pad(t.astype(np.float64), ((0, 0), (1, 1), (1, 1), (0, 0))) for t in (g, x))
+    with np.errstate(invalid="ignore", over="ignore"):
+        dw = np.stack([np.stack([(g.astype(np.float64)[..., :, None] * xp[:, r:r + h, s:s + v, None, :]).sum((0, 1, 2))
+                                 for s in range(3)], 1) for r in range(3)], 1)
+        dx = sum((gp[:, 2 - r:2 - r + h, 2 - s:2 - s + v, :, None] * w[:, r, s].astype(np.float64)).sum(3)
+                 for r in range(3) for s in range(3))
+        return dw, g.astype(np.float64).sum((0, 1, 2)), dx
+
+
+# per-tap staging (24 channels) and halo staging (64), input and weight gradients;
+# 289 pixels: two splits of the weight gradients.  mixed: the infinite terms of an
+# input gradient have both signs and meet as NaN, else it is an infinity
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("a,b", [(8, 24), (32, 64)])
+def test_infinite_gradients_pass_as_in_fp32(a, b, mixed):
+    """One channel of the last conv (residual) has an infinite gradient: two
+    classes with weights of +-3.4e38 there, one example, the wrong one right.
+    The input gradient (residual and ReLU mask included), the weight gradients
+    with it and, of what reaches the layer below, all gradients there are checked
+    against float64 from the GPU's own inputs of each pass."""
+    side, c = 17, 5
+    layers = [("conv", 3, a, False), ("conv", a, b, False), ("conv", b, b, True), ("avgpool",), ("linear", b, 4)]
+
+    images = np.random.default_rng(4).standard_normal((1, side, side, 3)).astype(np.float32)
+
+    def change(th):
+        th[4][c] *= np.float32(1e-3)  # a small channel (its logits stay finite), on at half the pixels
+        th[2][c], th[3][c], th[5][c] = 0, 0, 0
+        if not mixed:
+            th[4][c] = np.abs(th[4][c])
+        x = _conv(_conv(images.astype(np.float64), th[0], th[1]), th[2], th[3])
+        th[5][c] = -np.median(_conv(x, th[4][c:c + 1], np.array([1e3])) - 1e3)
+        th[6][1, c], th[6][2, c] = np.float32(-3.4e38), np.float32(3.4e38)
+
+    act, grad, _, _, th, gpre = _round(images, layers, side, change, labels=np.array([1], np.int32))
+    assert all(np.isfinite(x).all() for x in act)
+    live = act[2][..., c] > 0
+    assert 0 < live.sum() < live.size
+    assert np.isposinf(gpre[2][..., c][live]).all() and (gpre[2][..., c][~live] == 0).all()
+    assert np.isfinite(np.delete(gpre[2], c, 3)).all()
+    o = 0
+    for i in range(3):
+        x = images if i == 0 else act[i - 1]
+        dw, db, dx = _grads64(gpre[i], x, th[2 * i])
+        n = th[2 * i].size
+        _same(grad[o:o + n].reshape(th[2 * i].shape), dw)
+        _same(grad[o + n:o + n + len(db)], db)
+        o += n + len(db)
+        if i:
+            with np.errstate(invalid="ignore"):
+                dx = np.where(act[i - 1] > 0, dx + gpre[i] if i == 2 else dx, 0.0)
+            _same(gpre[i - 1], dx)
+    inf, nan = np.isinf(gpre[1]).sum(), np.isnan(gpre[1]).sum()
+    assert nan > 0 if mixed else inf > 0 and nan == 0
