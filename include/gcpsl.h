@@ -427,7 +427,7 @@ int gcpsl_tensor(gcpsl_ctx *ctx, const char *name, void **ptr, int64_t *numel, i
  * kernels (entries beyond cap are dropped).
  */
 typedef struct gcpsl_kernel_stat {
-  char name[64];    /* kernel instantiation, e.g. "conv_fwd<bf16,128x128,vec>" */
+  char name[64];    /* kernel instantiation, e.g. "conv_fwd<f32,128x64,w4,split>" */
   int64_t launches; /* launches aggregated                                    */
   double ms;        /* summed event time in milliseconds                      */
   double flops;     /* summed algorithmic FLOPs                               */

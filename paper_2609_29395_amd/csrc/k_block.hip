@@ -9,11 +9,11 @@
 //                gradient then take these rows as a one-tap product.
 //   zero_insert  (bf16, output channels that are no multiple of 64: the others
 //                take the gradient by classes of input pixels) a stride-2
-//                conv's output gradient spread back to the input grid: gup[b][h][w] = g[b][h/2][w/2] at even (h, w), zero
-//                elsewhere.  The input gradient of a 3x3 / pad 1 (or 1x1 /
-//                pad 0) conv with stride 2 is then the stride-1 input
-//                gradient of gup (the inserted zeros add exact zeros), on
-//                the stride-1 kernels.
+//                conv's output gradient spread back to the input grid:
+//                gup[b][h][w] = g[b][h/2][w/2] at even (h, w), zero elsewhere.
+//                The input gradient of a 3x3 / pad 1 (or 1x1 / pad 0) conv with
+//                stride 2 is then the stride-1 input gradient of gup (the
+//                inserted zeros add exact zeros), on the stride-1 kernels.
 // One 16-byte vector of channels per thread; grid (vectors / 256, replica
 // slots).  Channel counts are multiples of the vector width.
 #include "runtime.h"

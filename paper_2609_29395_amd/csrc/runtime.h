@@ -55,7 +55,7 @@ struct ConvArgs {
   const int32_t *rmap;  // device [C]: replica of each slot, or null (slot z = replica z)
   int epi;
   int taps;  // 9: 3x3 implicit GEMM; 1: src already holds im2col rows, A[m][k] = src[m][k]
-  int res_lds;  // set by the launcher: the residual (== src) is taken from the staged centre tap
+  int res_lds;  // set by the launcher (halo tiles): the residual (== src) is taken from the staged centre tap
   int no_relu;  // fwd: store the raw output (a norm layer follows)
   void *pool_out;      // fwd: also a pooling of the output, else null: the 2x2 max pool
                        // [C][Bt][H/2][W/2][N] (kernels that report conv_fuses_pool) or the mean over
